@@ -513,16 +513,20 @@ int batch_build(Batch& B) {
   for (int K = 0; K <= kMaxK; ++K)
     for (int items = 1; items <= 4; items *= 2) {
       std::vector<int2> it;
-      size_t l = 0;
+      size_t l = 0, state = 0;
+      int planes = 0;
       for (int s = 0; s < n; ++s) {
         const Plan& P = *B.scenes[s];
         if (P.npairs == 0 || P.prm.K != K || P.sweep.items != items) continue;
         const int c = sweep_blocks(P);
         for (int i = 0; i < c; ++i) it.push_back(make_int2(s, i));
         l = std::max(l, P.sweep.lds);
+        state += P.sz[B_SIGMA] + P.sz[B_SCODE];
+        planes = std::max(planes, P.npairs * P.npatch);
       }
       if (it.empty()) continue;
       if ((rc = add_group(B, KD_SWEEP, it, kSweepThreads, l, K, items))) return rc;
+      B.groups[KD_SWEEP].back().policy = sweep_policy(state, planes);
       if ((rc = sweep_prepare(K, items))) return rc;
     }
   NLPR_HIP_TRY(hipMalloc(&B.d_desc, n * sizeof(SceneDesc)));

@@ -107,6 +107,9 @@ constexpr int kSweepThreads = 256;   // workgroup size of the sweep
 // more than the overlap gains (256 x 256 x 31: 2.77 -> 2.90 ms per solve; 512 x 512 x 128:
 // 3.03 -> 2.98 s).
 constexpr size_t kForkPixelBands = (size_t)1 << 22;
+// Cache policies of the sweep's dual state: nothing, the packed values, or all of it bypass
+// the caches (non-temporal).
+enum SweepPolicy { kSweepCached = 0, kSweepCodesCached = 1, kSweepStream = 2 };
 // open-item counters of one sweep launch (timing plans): kCountSlots, kCountStride apart
 constexpr int kCountSlots = 64;
 constexpr int kCountStride = 16;
@@ -165,6 +168,7 @@ struct Group {
   int block = 256;
   size_t lds = 0;
   int key0 = 0, key1 = 0;   // sweep: K, items per thread
+  int policy = 0;           // sweep: cache policy of the dual state
 };
 
 enum Kind { KD_WEIGHTS = 0, KD_PLANE, KD_CONV, KD_PIXEL, KD_SWEEP, KD_ROWS, KD_COLS,
@@ -245,6 +249,7 @@ typedef __attribute__((address_space(1))) double gdouble;
 typedef float v2f_t __attribute__((ext_vector_type(2)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef int v2i_t __attribute__((ext_vector_type(2)));
+typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v2f_t gv2f;
 typedef __attribute__((address_space(1))) v4f_t gv4f;
 typedef __attribute__((address_space(1))) v2i_t gv2i;
@@ -377,6 +382,7 @@ int sweep_prepare(int K, int items);   // kernel attributes; before launches or 
 
 // ---- shapes and tuning
 SweepShape choose_sweep_shape(int p, int q, int K, int halo);
+int sweep_policy(size_t state, int planes);
 int choose_pair_split(int blocks, int npairs);   // SweepShape.split for `blocks` (tile, band) pairs
 size_t sweep_sigma_bytes(const SweepShape& sh, int q, int L, int npairs, int npatch);
 int fft_block(int tpl);             // workgroup size of a line FFT with tpl threads per line

@@ -80,7 +80,11 @@ __device__ __forceinline__ float clampf(float v, float m) { return fminf(fmaxf(v
 // packed per wave: the 64 items a wave owns in a plane (one 1 KB
 // segment of the plane) keep the float4s of their open items at the start of that segment,
 // in lane order, so a wave reads and writes only as many 16-byte slots as it has open
-// items (mbcnt of the ballot gives each open lane its slot).  A wave reads its whole old
+// items (mbcnt of the ballot gives each open lane its slot).  The last 64 bytes of a run are
+// written whole: up to three lanes without an open item write what they hold into the slots
+// after it, which nothing reads.  A part of a 64-byte block costs HBM a read of the rest
+// (first sweep of 512 x 512 x 16, write only: 2.77 ms with runs that end anywhere, 1.82 ms
+// with whole 64-byte blocks, 1.88 ms with whole 128-byte lines).  A wave reads its whole old
 // run before it writes the new one, and each segment belongs to one wave, so the update is
 // in place.  Decoding is exact: the stored values are the values, and -mu, +mu are the
 // thresholds that produced the on-threshold ones.
@@ -88,9 +92,10 @@ __device__ __forceinline__ float clampf(float v, float m) { return fminf(fmaxf(v
 // threshold it took, which is all the sweep's adjoint needs of this iteration: 2 bits, 0 for
 // |V| < mu, 1 for V >= mu, 2 for V <= -mu, 3 for V = 0 with mu = 0 (or V not a number).  The
 // four elements of a float4 item share one byte, at the item's float offset / 4.
-// COUNT: add the number of open items written by each wave to one of the kCountSlots
-// counters at count (kCountStride apart); their sum is the launch's count.
-template <int K, int ITEMS, int NT, bool FIRST, bool CODES>
+// count, if not null: add the number of open items written by each wave to one of the
+// kCountSlots counters there (kCountStride apart); their sum is the launch's count.
+// POLICY: which part of the dual state passes the caches by (sweep_policy).
+template <int K, int ITEMS, int NT, bool FIRST, bool CODES, int POLICY>
 __global__ void __launch_bounds__(NT)
 sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s, int mu_s,
              int sig_s, int code_s, int creg_s, int halo_s, uint8_t* codes,
@@ -127,15 +132,6 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
   gfloat* halo = gslot<gfloat>(S, halo_s) + (size_t)part * L * ntiles * H * q;
   const gfloat* Xc = X + (size_t)c * plane;
 
-  for (int e = threadIdx.x; e < (R + H) * q4; e += NT) {
-    const int rr = e / q4, c4 = e - rr * q4;
-    int gr = (r0 - H + rr) % p;
-    if (gr < 0) gr += p;
-    reinterpret_cast<float4*>(Xs)[e] = ldg4(Xc + (size_t)gr * q + 4 * c4);
-    reinterpret_cast<float4*>(Cs)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  __syncthreads();
-
   int row[ITEMS], col[ITEMS], seg[ITEMS];
   bool ok[ITEMS];
   float4 xv[ITEMS], cp[ITEMS];
@@ -146,8 +142,6 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
     col[m] = (it - row[m] * q4) * 4;
     seg[m] = 4 * (it & ~63);            // float offset of the wave's segment in a plane
     ok[m] = row[m] < rows;
-    xv[m] = ok[m] ? *reinterpret_cast<const float4*>(Xs + (row[m] + H) * q + col[m])
-                  : make_float4(0.f, 0.f, 0.f, 0.f);
     cp[m] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   unsigned open_written = 0;            // open items this wave wrote (wave-uniform)
@@ -197,7 +191,6 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
     const int2 tj = j < n_end ? tau_at(S, j) : make_int2(0, 0);
     tau_lane = (tj.x << 16) | (tj.y & 0xffff);
   };
-  tau_fetch(n_begin);
 
   // With one item per thread the planes are software-pipelined.  The planes of a workgroup
   // form one contiguous sequence over its shifts (plane x at base + x kstride); while plane x
@@ -207,46 +200,71 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
   // number of memory operations after each is fixed and the wait for plane x leaves the later
   // ones in flight.  A plane is read only before it is written: its own requests come D and
   // D + E planes earlier, repeats of the last plane up to its own update.
+  // A request that is still in flight at the end of a shift must land in the register its
+  // plane is read from in the next one: a copy there would wait for the request (and, the
+  // counter being in order, for all before it).  The registers turn over once per shift of NP
+  // planes, so this needs D + E <= NP; at 3 x 3 D = E = 6 (12 > 9) drained the pipeline at
+  // the end of every shift.
   constexpr bool PIPE = !FIRST && ITEMS == 1;
-  constexpr int D = K <= 1 ? 6 : 5, E = D;
+  constexpr int D = K == 0 ? 6 : K == 1 ? 4 : 5, E = D;
   const int nplanes = (n_end - n_begin) * NP;
   const size_t base = tile_off + (size_t)n_begin * tstride;
-  uint8_t cq[D + E + 1];   // code bytes of planes x .. x + D + E (kept as bytes: a widening
-                           // at the loop's back edge would wait for the loads in flight)
-  float4 sb[D + 1];        // open float4s of planes x .. x + D
-  // the workgroup's code bytes as one buffer, plane x at byte x * cstride: a lane's byte is
-  // addressed by the plane offset (a scalar) and the thread index, with no vector arithmetic
-  // (accesses past the range would be dropped)
+  constexpr bool RING = NP > D + E;
+  uint8_t cq[RING ? NP : D + E + 1];   // code bytes of planes x .. x + D + E (kept as bytes: a
+                                       // widening at the loop's back edge would wait)
+  float4 sb[RING ? NP : D + 1];        // open float4s of planes x .. x + D
+  unsigned long long oq[RING ? NP : D + 1];   // and their ballots
+  // With one item per thread the workgroup's code bytes and its packed values are one buffer
+  // each, plane x at byte x * cstride and 16 x * cstride (at most 11 664 planes of 4 KB: 32
+  // bits): a lane's address is the plane offset (a scalar that grows by one stride per plane)
+  // plus a 32-bit lane offset, with no 64-bit arithmetic.  Accesses past the range are
+  // dropped and read zero, which is what the lanes past the tile get (coff).
+  constexpr bool BUF = ITEMS == 1;
+  constexpr int POL = POLICY != kSweepCached ? kCacheNT : 0;    // packed values
+  constexpr int CPOL = POLICY == kSweepStream ? kCacheNT : 0;   // code bytes
   const unsigned cstride = (unsigned)(kstride >> 2);
+  const unsigned clast = (unsigned)max(nplanes - 1, 0) * cstride;   // the last plane
   const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(uint8_t*)(scode + (base >> 2)), (short)0, PIPE ? nplanes * (int)cstride : 0,
+      (void*)(uint8_t*)(scode + (base >> 2)), (short)0, BUF ? nplanes * (int)cstride : 0,
       kRawBufferFlags);
-  auto pipe_codes = [&](int x) -> uint8_t {
-    return __builtin_amdgcn_raw_buffer_load_b8(crs, threadIdx.x, min(x, nplanes - 1) * cstride,
-                                               kCacheNT);
+  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(float*)(sig + base), (short)0, BUF ? 16 * nplanes * (int)cstride : 0,
+      kRawBufferFlags);
+  const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
+      CODES ? (void*)(codes + (base >> 2)) : nullptr, (short)0,
+      BUF && CODES ? nplanes * (int)cstride : 0, kRawBufferFlags);
+  const unsigned coff = ok[0] ? threadIdx.x : 0x7fffffffu;
+  // requests of the plane at code offset co, or of the last plane if that is before it
+  auto pipe_codes = [&](unsigned co) -> uint8_t {
+    return __builtin_amdgcn_raw_buffer_load_b8(crs, coff, min(co, clast), CPOL);
   };
-  // the ballot of a plain comparison is one instruction: the lanes past the tile are cleared
-  // with a mask taken once; each lane without an open item reads the slot after the open
-  // lanes below it, inside the segment
-  const unsigned long long okmask = __builtin_amdgcn_ballot_w64(ok[0]);
+  // each lane without an open item reads the slot after the open lanes below it, inside the
+  // segment
   const unsigned segb = 4u * (unsigned)seg[0];  // byte offset of the wave's segment
-  auto pipe_open = [&](int x, unsigned cx) -> float4 {
-    const gfloat* pb = sig + base + (size_t)min(x, nplanes - 1) * kstride;
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(cx >= 16u) & okmask;
+  auto pipe_open = [&](unsigned co, unsigned cx, unsigned long long& bal) -> float4 {
+    bal = __builtin_amdgcn_ballot_w64(cx >= 16u);
     const unsigned slot = __builtin_amdgcn_mbcnt_hi(
         (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-    return ld_nt((const gfloat*)((const gu8*)pb + (segb + 16u * slot)));
+    const v4u_t v = __builtin_amdgcn_raw_buffer_load_b128(vrs, segb + 16u * slot,
+                                                          16u * min(co, clast), POL);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                       __uint_as_float(v.w));
   };
-  if constexpr (PIPE) {
-    if (nplanes > 0) {
+  // what the lane's wave may store of the segment of item it: its items in the plane, and the
+  // position of the workgroup's first item in a 64-byte block
+  const unsigned okn = (unsigned)(R * q4), a0 = (unsigned)(base >> 2) & 3u;
+  auto seg_cap = [&](int m) -> unsigned {
+    const unsigned s0 = __builtin_amdgcn_readfirstlane(threadIdx.x + NT * m) & ~63u;
+    return s0 < okn ? min(64u, okn - s0) : 0u;
+  };
+  unsigned cap[ITEMS];
+  unsigned long long okmask[ITEMS];
 #pragma unroll
-      for (int i = 0; i < D + E; ++i) cq[i] = pipe_codes(i);
-#pragma unroll
-      for (int i = 0; i < D; ++i) sb[i] = pipe_open(i, cq[i]);
-    }
-  } else if (!FIRST && n_begin < n_end) {
-    load_codes(tile_off + (size_t)n_begin * tstride);
+  for (int m = 0; m < ITEMS; ++m) {
+    cap[m] = seg_cap(m);
+    okmask[m] = __builtin_amdgcn_ballot_w64(ok[m]);
   }
+  const unsigned lane = threadIdx.x & 63u;
 
   // thresholds mu(., tau) of the tile rows and their K halo, (R + 2K) q4 float4s per shift.
   // When they fit MUR per thread their offsets in a mu plane are computed once (no integer
@@ -273,8 +291,51 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
     for (int u = 0; u < MUR; ++u)
       if (mu_off[u] >= 0) mv[MU_AHEAD ? u : 0] = ldg4(mun + mu_off[u]);
   };
+  // All first requests before the first wait: the codes of the first planes, the shifts, the
+  // first thresholds and the tile of X; then the values that the codes place.
+  if constexpr (PIPE) {
+    if (nplanes > 0) {
+#pragma unroll
+      for (int i = 0; i < D + E; ++i) cq[i] = pipe_codes(i * cstride);
+    }
+  } else if (!FIRST && n_begin < n_end) {
+    load_codes(tile_off + (size_t)n_begin * tstride);
+  }
+  tau_fetch(n_begin);
   if (MU_AHEAD && mu_hoist && n_begin < n_end) mu_fetch(n_begin);
+  constexpr int XU = 4;
+  for (int e0 = threadIdx.x; e0 < (R + H) * q4; e0 += XU * NT) {
+    float4 t[XU];
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+      const int e = min(e0 + u * NT, (R + H) * q4 - 1);
+      const int rr = e / q4, c4 = e - rr * q4;
+      int gr = (r0 - H + rr) % p;
+      if (gr < 0) gr += p;
+      t[u] = ldg4(Xc + (size_t)gr * q + 4 * c4);
+    }
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+      const int e = e0 + u * NT;
+      if (e < (R + H) * q4) {
+        reinterpret_cast<float4*>(Xs)[e] = t[u];
+        reinterpret_cast<float4*>(Cs)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+  }
+  if constexpr (PIPE) {
+    if (nplanes > 0) {
+#pragma unroll
+      for (int i = 0; i < D; ++i) sb[i] = pipe_open(i * cstride, cq[i], oq[i]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < ITEMS; ++m)
+    xv[m] = ok[m] ? *reinterpret_cast<const float4*>(Xs + (row[m] + H) * q + col[m])
+                  : make_float4(0.f, 0.f, 0.f, 0.f);
 
+  unsigned co = 0;                      // code offset of the current plane
   for (int n = n_begin; n < n_end; ++n) {
     if (n > n_begin && ((n - n_begin) & 63) == 0) tau_fetch(n);
     const int tpk = __builtin_amdgcn_readlane(tau_lane, (n - n_begin) & 63);
@@ -365,26 +426,40 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
           float sv[4];
           unsigned cbv = 0;  // this plane's old code byte and open float4
           float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
-          const int x = (n - n_begin) * NP + (k1 + K) * KW + k2;  // plane of the workgroup
+          bool open = false;
           if constexpr (PIPE) {
-            cq[D + E] = pipe_codes(x + D + E);
-            sb[D] = pipe_open(x + D, cq[D]);
-            cbv = cq[0];
-            s4 = sb[0];
+            if constexpr (RING) {
+              const int kk = (k1 + K) * KW + k2;   // plane of the shift: known when unrolled
+              cq[(kk + D + E) % NP] = pipe_codes(co + (D + E) * cstride);
+              sb[(kk + D) % NP] =
+                  pipe_open(co + D * cstride, cq[(kk + D) % NP], oq[(kk + D) % NP]);
+              cbv = cq[kk];
+              s4 = sb[kk];
+              open = __builtin_amdgcn_inverse_ballot_w64(oq[kk]);
+            } else {
+              cq[D + E] = pipe_codes(co + (D + E) * cstride);
+              sb[D] = pipe_open(co + D * cstride, cq[D], oq[D]);
+              cbv = cq[0];
+              s4 = sb[0];
+              open = __builtin_amdgcn_inverse_ballot_w64(oq[0]);
 #pragma unroll
-            for (int i = 0; i < D + E; ++i) cq[i] = cq[i + 1];
+              for (int i = 0; i < D + E; ++i) cq[i] = cq[i + 1];
 #pragma unroll
-            for (int i = 0; i < D; ++i) sb[i] = sb[i + 1];
+              for (int i = 0; i < D; ++i) {
+                sb[i] = sb[i + 1];
+                oq[i] = oq[i + 1];
+              }
+            }
           } else if (!FIRST) {
             cbv = cb[k2][m];
             s4 = s[k2][m];
+            open = ok[m] && cbv >= 16u;
           }
           if (FIRST) {
             sv[0] = sv[1] = sv[2] = sv[3] = 0.f;
           } else {
             // sv = -Sigma' = clip(V_old, +-mu): the stored value, or on the threshold mu with
             // the sign of V_old (bit e), i.e. mu's magnitude under that sign bit
-            const bool open = ok[m] && cbv >= 16u;
             const float st[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -416,31 +491,42 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
 #pragma unroll
           for (int e = 3; e >= 0; --e)
             code = __builtin_amdgcn_alignbit(code, __float_as_uint(vv[e]), 31);
-          if (ok[m]) {
-            A[m].x += acc[0];
-            A[m].y += acc[1];
-            A[m].z += acc[2];
-            A[m].w += acc[3];
-          }
-          const bool opn = ok[m] && code >= 16u;
-          if (opn) {
-            // inside the branch the execution mask is the ballot of the open lanes (every
-            // lane of the wave reaches this point)
-            const unsigned long long bal = __builtin_amdgcn_read_exec();
+          A[m].x += acc[0];   // lanes past the tile too: they never use it
+          A[m].y += acc[1];
+          A[m].z += acc[2];
+          A[m].w += acc[3];
+          // (in place: the additions must not sink to their use at the end of the shift)
+          asm volatile("" : "+v"(A[m].x), "+v"(A[m].y), "+v"(A[m].z), "+v"(A[m].w));
+          const unsigned long long bal = __builtin_amdgcn_ballot_w64(code >= 16u) & okmask[m];
+          const unsigned nopen = (unsigned)__builtin_popcountll(bal);
+          open_written += nopen;
+          if (bal) {
+            // the open lanes in lane order, then lanes without an open item up to the end of
+            // the last 64-byte block (at most the segment's items)
             const unsigned slot = __builtin_amdgcn_mbcnt_hi(
                 (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-            st_nt(vb + (seg[m] + 4u * slot), make_float4(nv[0], nv[1], nv[2], nv[3]));
+            const unsigned at = BUF ? co + a0 : (unsigned)(pl_off >> 2);
+            const unsigned lim = min(((at + nopen + 3u) & ~3u) - at, cap[m]);
+            const unsigned to =
+                __builtin_amdgcn_inverse_ballot_w64(bal) ? slot : nopen + lane - slot;
+            if (to < lim) {
+              if constexpr (BUF) {
+                const v4u_t w = {__float_as_uint(nv[0]), __float_as_uint(nv[1]),
+                                 __float_as_uint(nv[2]), __float_as_uint(nv[3])};
+                __builtin_amdgcn_raw_buffer_store_b128(w, vrs, segb + 16u * to, 16u * co, POL);
+              } else {
+                st_nt(vb + (seg[m] + 4u * to), make_float4(nv[0], nv[1], nv[2], nv[3]));
+              }
+            }
           }
-          if (count)
-            open_written += (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(opn));
-          if (ok[m]) {
-            if constexpr (PIPE)
-              __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, crs, threadIdx.x, x * cstride,
-                                                   kCacheNT);
-            else
-              __builtin_nontemporal_store((uint8_t)code, cbp + (threadIdx.x + NT * m));
-            if (CODES) ((gu8*)codes)[(pl_off >> 2) + threadIdx.x + NT * m] = (uint8_t)branch;
+          if constexpr (BUF) {
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, crs, coff, co, CPOL);
+            if (CODES)
+              __builtin_amdgcn_raw_buffer_store_b8((uint8_t)branch, brs, coff, co, 0);
+          } else if (ok[m]) {
+            __builtin_nontemporal_store((uint8_t)code, cbp + (threadIdx.x + NT * m));
           }
+          co += cstride;
         }
       }
     }
@@ -494,10 +580,10 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
 // 128 threads with two items each (89 against 154 VGPRs at the time: five waves per SIMD
 // instead of three; 20-iteration solve 2.88 against 3.16 ms).
 
-template <int K, int ITEMS, int NT, bool FIRST, bool CODES>
+template <int K, int ITEMS, int NT, bool FIRST, bool CODES, int POLICY>
 int launch_k(const Batch& B, const Group& g, int x, int mu, int sig, int creg, int halo,
              uint8_t* codes, unsigned long long* count, hipStream_t s) {
-  auto kern = sweep_kernel<K, ITEMS, NT, FIRST, CODES>;
+  auto kern = sweep_kernel<K, ITEMS, NT, FIRST, CODES, POLICY>;
   hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(NT), g.lds, s, B.d_desc, g.d_items, x, mu,
                      sig, (int)B_SCODE, creg, halo, codes, count);
   NLPR_LAUNCH_CHECK("sweep_kernel");
@@ -506,45 +592,73 @@ int launch_k(const Batch& B, const Group& g, int x, int mu, int sig, int creg, i
 
 // Allow the sweep's dynamic LDS beyond the default limit (done when a batch is built, not
 // during graph capture).  The branch-recording variant exists for single-item tiles.
-template <int K, int ITEMS, int NT>
+template <typename Kern>
+int lds_limit(Kern kern) {
+  NLPR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)kMaxSweepLds));
+  return NLPR_OK;
+}
+
+template <int K, int ITEMS, int NT, int POLICY>
 int set_lds_limit() {
-  const bool single = ITEMS == 1;
-  const void* kern[4] = {
-      reinterpret_cast<const void*>(sweep_kernel<K, ITEMS, NT, true, false>),
-      reinterpret_cast<const void*>(sweep_kernel<K, ITEMS, NT, false, false>),
-      single ? reinterpret_cast<const void*>(sweep_kernel<K, ITEMS, NT, true, true>) : nullptr,
-      single ? reinterpret_cast<const void*>(sweep_kernel<K, ITEMS, NT, false, true>) : nullptr};
-  for (const void* k : kern)
-    if (k) NLPR_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)kMaxSweepLds));
+  int rc;
+  if ((rc = lds_limit(sweep_kernel<K, ITEMS, NT, true, false, POLICY>)) ||
+      (rc = lds_limit(sweep_kernel<K, ITEMS, NT, false, false, POLICY>)))
+    return rc;
+  if constexpr (ITEMS == 1)
+    if ((rc = lds_limit(sweep_kernel<K, ITEMS, NT, true, true, POLICY>)) ||
+        (rc = lds_limit(sweep_kernel<K, ITEMS, NT, false, true, POLICY>)))
+      return rc;
   return NLPR_OK;
 }
 
 template <int K>
 int set_lds_limit_items(int items) {
+  constexpr int NT = kSweepThreads;
+  int rc;
   switch (items) {
-    case 1: return set_lds_limit<K, 1, kSweepThreads>();
-    case 2: return set_lds_limit<K, 2, kSweepThreads>();
-    default: return set_lds_limit<K, 4, kSweepThreads>();
+    case 1:
+      if ((rc = set_lds_limit<K, 1, NT, kSweepCached>()) ||
+          (rc = set_lds_limit<K, 1, NT, kSweepCodesCached>()))
+        return rc;
+      return set_lds_limit<K, 1, NT, kSweepStream>();
+    case 2: return set_lds_limit<K, 2, NT, kSweepStream>();
+    default: return set_lds_limit<K, 4, NT, kSweepStream>();
   }
 }
 
-// g.key1 = tile items
+// g.key1 = tile items, g.policy = the cache policy of single-item tiles
+template <int K, bool FIRST, int POLICY>
+int launch_single(const Batch& B, const Group& g, int x, int mu, int sig, int creg, int halo,
+                  uint8_t* codes, unsigned long long* count, hipStream_t s) {
+  constexpr int NT = kSweepThreads;
+  return codes ? launch_k<K, 1, NT, FIRST, true, POLICY>(B, g, x, mu, sig, creg, halo, codes, count, s)
+               : launch_k<K, 1, NT, FIRST, false, POLICY>(B, g, x, mu, sig, creg, halo, codes, count, s);
+}
+
 template <int K, bool FIRST>
 int launch_items(const Batch& B, const Group& g, int x, int mu, int sig, int creg, int halo,
                  uint8_t* codes, unsigned long long* count, hipStream_t s) {
+  constexpr int NT = kSweepThreads;
   if (codes && g.key1 != 1) {
     set_error("sweep: branch codes need single-item tiles");
     return NLPR_ERR_UNSUPPORTED_SHAPE;
   }
-  if (codes) return launch_k<K, 1, kSweepThreads, FIRST, true>(B, g, x, mu, sig, creg, halo, codes, count, s);
   switch (g.key1) {
     case 1:
-      return launch_k<K, 1, kSweepThreads, FIRST, false>(B, g, x, mu, sig, creg, halo, nullptr, count, s);
+      switch (g.policy) {
+        case kSweepCached:
+          return launch_single<K, FIRST, kSweepCached>(B, g, x, mu, sig, creg, halo, codes, count, s);
+        case kSweepCodesCached:
+          return launch_single<K, FIRST, kSweepCodesCached>(B, g, x, mu, sig, creg, halo, codes, count, s);
+        default:
+          return launch_single<K, FIRST, kSweepStream>(B, g, x, mu, sig, creg, halo, codes, count, s);
+      }
     case 2:
-      return launch_k<K, 2, kSweepThreads, FIRST, false>(B, g, x, mu, sig, creg, halo, nullptr, count, s);
+      return launch_k<K, 2, NT, FIRST, false, kSweepStream>(B, g, x, mu, sig, creg, halo, nullptr, count, s);
     default:
-      return launch_k<K, 4, kSweepThreads, FIRST, false>(B, g, x, mu, sig, creg, halo, nullptr, count, s);
+      return launch_k<K, 4, NT, FIRST, false, kSweepStream>(B, g, x, mu, sig, creg, halo, nullptr, count, s);
   }
 }
 
@@ -573,6 +687,26 @@ int choose_pair_split(int blocks, int npairs) {
   constexpr int kCus = 256;
   if (blocks <= 0 || blocks >= kCus || npairs <= 1) return 1;
   return std::min(npairs, (kCus + blocks - 1) / blocks);
+}
+
+// Cache policy of a sweep launch over `state` bytes of dual state (capacity, all scenes) with
+// `planes` planes per band.  The lines lie where they are measured; sweep per launch, MI355X:
+// - up to 384 MB, of which a launch touches about half, the state stays in the 256 MB
+//   Infinity Cache from one sweep to the next when it is not streamed: 256 x 256 x 31 3x3/3x3
+//   (312 MB) 65 us streamed, 54 us cached; 192 x 256 x 31 (233 MB) 51 and 40 us; but
+//   256 x 256 x 46 (461 MB) 3.74 and 3.79 ms per 20-iteration solve, and 1024 x 1024 x 4 with a
+//   5x5 window (1.9 GB) 597 and 727 us.
+// - above that the values are streamed.  The code bytes (1/17 of the state, read and written
+//   64 bytes per wave) gain from the caches, which also join stores that are not whole 64-byte
+//   blocks: 108 x 144 x 31 5x5/5x5 151 us streamed, 139 us cached; 512 x 512 x 16 5x5/11x11
+//   2.91 and 2.83 ms.  But they push the dense planes out of the caches, which counts where the
+//   sweep does not carry the iteration: 256 x 256 x 124 3x3/3x3 (1.2 GB) 9.1 ms per solve
+//   streamed, 9.5 ms cached.  So the codes are streamed for more than 1 GB of state in planes
+//   so few (under 200) that the other stages matter.
+int sweep_policy(size_t state, int planes) {
+  if (state <= (size_t)384 << 20) return kSweepCached;
+  if (state <= (size_t)1 << 30 || planes >= 200) return kSweepCodesCached;
+  return kSweepStream;
 }
 
 int sweep_blocks(const Plan& P) { return P.sweep.ntiles * P.Lx * P.sweep.split; }

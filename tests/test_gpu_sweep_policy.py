@@ -1,0 +1,67 @@
+"""Cache policies of the sweep's dual state: a launch over little state keeps it in the caches,
+larger ones stream the packed values, or the values and the code bytes.  The policy follows the
+whole launch, so a scene solved in a batch with a large one runs under the large one's policy;
+its iterates must not change by a bit, and its decoded dual state neither.  The shapes have
+partial tiles, segments of less than 64 items and planes that do not start on 64 bytes, where a
+packed run ends at the capacity of its segment."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_2210_04184_amd import nlpr
+
+pytestmark = pytest.mark.gpu
+
+SMALL = [dict(p=24, q=36, L=5, Lh=2, d=4, blur_radius=2, K=1, Sw=2, iters=6, seed=3),
+         dict(p=18, q=108, L=3, Lh=1, d=3, blur_radius=1, K=2, Sw=1, iters=6, seed=4),
+         dict(p=16, q=384, L=4, Lh=1, d=4, blur_radius=3, K=1, Sw=1, iters=6, seed=5)]
+# a scene that takes the launch above 384 MiB of dual state, and one that takes it above 1 GiB
+# (with fewer than 200 planes per band)
+FILLER = {"codes cached": dict(p=256, q=256, L=44, Lh=1, d=4, blur_radius=1, K=1, Sw=1, iters=6),
+          "streamed": dict(p=256, q=256, L=116, Lh=1, d=4, blur_radius=1, K=1, Sw=1, iters=6)}
+
+
+def _inputs(sc):
+    return torch.from_numpy(sc.Yl).cuda(), torch.from_numpy(sc.Yh).cuda()
+
+
+@pytest.mark.parametrize("policy", sorted(FILLER))
+def test_policy_does_not_change_a_scene(policy):
+    scenes = [synth.make_scene(synth.small_spec(**kw)) for kw in SMALL if kw["K"] == 1]
+    filler = synth.make_scene(synth.small_spec(**FILLER[policy]))
+    single = []
+    for sc in scenes:
+        plan = nlpr.Plan.from_scene(sc)
+        Z, ws = plan.solve(*_inputs(sc))
+        single.append((Z, plan.state_sigma(ws)))
+    both = scenes + [filler]
+    batch = nlpr.Batch.from_scenes(both)
+    ins = [_inputs(sc) for sc in both]
+    Zs, ws = batch.solve([a for a, _ in ins], [b for _, b in ins])
+    for i, sc in enumerate(scenes):
+        assert torch.equal(Zs[i], single[i][0])
+        plan = nlpr.Plan.from_scene(sc)
+        part = lambda r: (lambda o, n: ws[o:o + n])(*batch.region(i, r))
+        sig = plan.sigma_expand(part(nlpr.REGION_SIGMA).view(torch.float32),
+                                part(nlpr.REGION_SIGMA_CODES),
+                                part(nlpr.REGION_MU).view(torch.float32))
+        assert torch.equal(sig, single[i][1])
+
+
+@pytest.mark.parametrize("kw", SMALL, ids=lambda kw: f"{kw['p']}x{kw['q']}")
+def test_packed_runs_stay_in_their_segments(kw):
+    """Every slot past a segment's items keeps what it held: the runs are written in whole
+    64-byte blocks, but never past the capacity of their segment (a write there would land in
+    the next plane's first run)."""
+    sc = synth.make_scene(synth.small_spec(**kw))
+    plan = nlpr.Plan.from_scene(sc)
+    Yl, Yh = _inputs(sc)
+    Z, ws = plan.solve(Yl, Yh)
+    sig = plan.state_sigma(ws)
+    mu = plan.region_view(ws, nlpr.REGION_MU).reshape(-1, kw["p"], kw["q"])
+    K = kw["K"]
+    for k in range((2 * K + 1) ** 2):
+        thr = torch.roll(mu, (K - k // (2 * K + 1), K - k % (2 * K + 1)), (-2, -1))
+        assert bool((sig[:, k].abs() <= thr[:, None]).all())
+    assert np.isfinite(Z.cpu().numpy()).all()

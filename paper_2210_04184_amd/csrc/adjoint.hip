@@ -16,21 +16,10 @@
 namespace nlpr {
 namespace {
 
-constexpr int PADW = 4;   // LDS column padding of the mu' accumulator (K <= 4)
-
 __device__ __forceinline__ int wrapg(int a, int m) {
   a %= m;
   return a < 0 ? a + m : a;
 }
-__device__ __forceinline__ float4 ld4_nt(const gfloat* p) {
-  const v4f_t v = __builtin_nontemporal_load((const gv4f*)p);
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void st4_nt(gfloat* p, float4 v) {
-  v4f_t w = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(w, (gv4f*)p);
-}
-
 // Sum of v[k] over the NW waves of the workgroup, in a fixed order; thread 0 gets it.
 template <int N, int NW>
 __device__ __forceinline__ void block_sum_waves(double (&v)[N]) {
@@ -86,43 +75,55 @@ __device__ __forceinline__ void block_sum256(double (&v)[N]) {
 // Coded Sigma'': outside the threshold the new Sigma''(j) = -(A'(j) + 0) depends on the shift
 // and the pixel only, so a float4 item is stored only if one of its elements is inside
 // (branch 0), packed per wave segment as the forward's open items (ballot and mbcnt give the
-// slots).  The next backward step, which has the branch codes of this step (pcodes) and this
-// step's C' (cbp_s), rebuilds the others with the same operations, so the values are exact.
+// slots, and the last 64 bytes of a run are written whole).  The next backward step, which has
+// the branch codes of this step (pcodes) and this step's C' (cbp_s), rebuilds the others with
+// the same operations, so the values are exact.
 // FIRST: the first backward step, whose incoming Sigma'' is zero.
 // The planes of a workgroup are software-pipelined as in the forward sweep: the codes of this
 // step and Sigma'' of plane x + D, and the codes of the previous step of plane x + D + E
 // (which place the packed float4s), are in flight while plane x is updated.  The requests
-// are issued on every path (lanes past the tile read the plane's first item, a wave with no
-// stored item the start of its segment, and past the last plane the last plane again,
-// unused), so each wait leaves the later requests in flight.  A plane is read before it is
-// written.
-template <int K, bool FIRST>
-__global__ void __launch_bounds__(256)
+// are issued on every path (lanes past the tile address past the buffer and read zero, a wave
+// with no stored item reads the start of its segment, and past the last plane the last plane
+// again, unused), so each wait leaves the later requests in flight.  A plane is read before it
+// is written.
+// mu': the 2K + 1 patch offsets of one patch row k1 reach columns col - K .. col + 3 + K of image row
+// row + k1.  A thread adds them up in registers; then it takes what its left and right
+// neighbours reach of its own four columns (through LDS) and adds its float4 of the row to the
+// tile.  So the tile takes one 16-byte read and write per patch row and thread, and one barrier
+// (with a read and write per patch offset and element, and a barrier per offset, the LDS
+// pipe with its bank conflicts was as busy as the vector units).
+// CACHED: Sigma'' is not streamed past the caches (the forward sweep's rule).
+// Bound by the latency of its requests at four waves per SIMD and by instruction issue: at
+// 256 x 256 x 31, 3x3/3x3, 62 us per launch (83 us with streamed runs that end anywhere, the
+// mu' tile read after the planes' requests and a read and write of it per offset).  Two planes
+// ahead (128 VGPRs) was best: 3 ahead takes 140 VGPRs and 68 us, 4 ahead 64 us, 3 ahead held
+// to 128 VGPRs spills and takes 75 us.
+template <int K, bool FIRST, bool CACHED>
+__global__ void __launch_bounds__(256, K <= 1 ? 4 : 1)
 sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int cb_s,
                  const uint8_t* codes, int sb_s, int xr_s, int halo_s, int mup_s,
                  const uint8_t* pcodes, int cbp_s) {
   constexpr int NT = 256;
   constexpr int KW = 2 * K + 1;
   constexpr int NP = KW * KW;
+  constexpr int POL = CACHED ? 0 : kCacheNT;
   const int2 it_ = items[blockIdx.x];
   const SceneDesc& S = sd[it_.x];
   const int p = S.p, q = S.q, L = S.L, npairs = S.npairs, R = S.rows, ntiles = S.ntiles,
             H = S.halo;
   const gfloat* Cb = gslot<const gfloat>(S, cb_s);
-  const gu8* cod = (const gu8*)codes;
-  const gu8* pcod = (const gu8*)pcodes;
   gfloat* sb = gslot<gfloat>(S, sb_s);
   gfloat* mup = gslot<gfloat>(S, mup_s);
   extern __shared__ float4 lds4[];
   float* lds = reinterpret_cast<float*>(lds4);
   const int q4 = q >> 2;
-  const int ms = q + 2 * PADW;
   const int ER = R + 2 * K;               // extended rows of the mu' tile
-  float* Mb = lds;                        // ER x ms   mu' accumulator
-  float* Cs = Mb + ER * ms;               // (R + H) x q   C'
+  float* Mb = lds;                        // ER x q   mu' accumulator
+  float* Cs = Mb + ER * q;                // (R + H) x q   C'
   float* As = Cs + (R + H) * q;           // (R + H) x q   X' accumulator
   float* Cps = As + (R + H) * q;          // (R + H) x q   C' of the previous step (not FIRST)
-  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float* Eg = Cps + (FIRST ? 0 : (R + H) * q);   // [2][2 K][NT] what threads reach beyond their
+                                                 // columns: left, then right
 
   // the forward sweep's work items, y = (tile * psplit + part) * L + band; the adjoint covers
   // all shifts of a tile in one workgroup, so the items of parts 1 .. psplit-1 have no work
@@ -135,26 +136,15 @@ sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ item
   const size_t plane = (size_t)p * q;
   const gfloat* Cc = Cb + (size_t)c * plane;
   const gfloat* Cpc = FIRST ? Cc : gslot<const gfloat>(S, cbp_s) + (size_t)c * plane;
-  for (int e = threadIdx.x; e < (R + H) * q4; e += NT) {
-    const int rr = e / q4, c4 = e - rr * q4;
-    const int gr = wrapg(r0 - H + rr, p);
-    reinterpret_cast<float4*>(Cs)[e] = ldg4(Cc + (size_t)gr * q + 4 * c4);
-    reinterpret_cast<float4*>(As)[e] = zero4;
-    if (!FIRST) reinterpret_cast<float4*>(Cps)[e] = ldg4(Cpc + (size_t)gr * q + 4 * c4);
-  }
-  __syncthreads();
 
   const int row = threadIdx.x / q4;
-  const int col = (threadIdx.x - row * q4) * 4;
+  const int c4 = threadIdx.x - row * q4;
+  const int col = c4 * 4;
   const bool ok = row < rows;
-  const float4 cv = ok ? *reinterpret_cast<const float4*>(Cs + (row + H) * q + col) : zero4;
-  const float4 cvp =
-      ok && !FIRST ? *reinterpret_cast<const float4*>(Cps + (row + H) * q + col) : zero4;
-  float4 cp = zero4;
+  float4 cp = make_float4(0.f, 0.f, 0.f, 0.f);
 
   const size_t kstride = (size_t)R * q;
-  const size_t tstride = (size_t)NP * kstride;
-  const size_t tile_off = ((size_t)c * ntiles + tile) * (size_t)npairs * tstride;
+  const size_t tile_off = ((size_t)c * ntiles + tile) * (size_t)npairs * NP * kstride;
   gfloat* mup_tile = mup + ((size_t)c * ntiles + tile) * (size_t)npairs * ER * q;
 
   // the shifts, one per lane, 64 at a time, packed as (tau1 << 16 | tau2): a load inside the
@@ -165,111 +155,199 @@ sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ item
     const int2 tj = j < npairs ? tau_at(S, j) : make_int2(0, 0);
     tau_lane = (tj.x << 16) | (tj.y & 0xffff);
   };
-  tau_fetch(0);
 
   // an item with a zero 2-bit field (an element inside the threshold) is stored
   auto stored = [](unsigned b) { return ((b | (b >> 1)) & 0x55u) != 0x55u; };
-  constexpr int D = 2, E = FIRST ? 0 : 2;
+  // the registers of the requests in flight turn over once per shift of NP planes (copies at
+  // the end of a shift would wait for them): D + E < NP
+  constexpr int D = 2, E = FIRST ? 0 : D;
+  constexpr bool RING = NP > D + E;
   const int nplanes = npairs * NP;
-  const unsigned itm = ok ? threadIdx.x : 0u;               // the lane's item in a plane
-  const unsigned segf = 4u * (threadIdx.x & ~63u);          // float offset of its wave segment
+  const unsigned segb = 16u * (threadIdx.x & ~63u);         // byte offset of its wave segment
+  const unsigned lane = threadIdx.x & 63u;
   const unsigned long long okmask = __builtin_amdgcn_ballot_w64(ok);
-  auto pbase = [&](int x) { return tile_off + (size_t)min(x, nplanes - 1) * kstride; };
-  unsigned cq[D + 1];          // this step's branch codes of planes x .. x + D
-  unsigned pq[D + E + 1];      // the previous step's codes of planes x .. x + D + E
-  float4 sq[D + 1];            // packed Sigma'' of planes x .. x + D
-  auto req_codes = [&](int x, unsigned& cw) { cw = (cod + (pbase(x) >> 2))[itm]; };
-  auto req_pcodes = [&](int x, unsigned& pw) { pw = (pcod + (pbase(x) >> 2))[itm]; };
-  auto req_sigma = [&](int x, unsigned pw, float4& sv) {
-    const unsigned long long bal = __builtin_amdgcn_ballot_w64(stored(pw)) & okmask;
+  const unsigned s0 = __builtin_amdgcn_readfirstlane(threadIdx.x) & ~63u;
+  const unsigned okn = (unsigned)(R * q4);
+  const unsigned cap = s0 < okn ? min(64u, okn - s0) : 0u;  // slots of the wave's segment
+  const unsigned a0 = (unsigned)(tile_off >> 2) & 3u;       // of its 64-byte block
+  const unsigned cstride = (unsigned)(kstride >> 2);
+  const unsigned clast = (unsigned)max(nplanes - 1, 0) * cstride;
+  auto rsrc = [&](const void* b, unsigned unit) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(b), (short)0,
+                                             (int)(unit * nplanes * cstride), kRawBufferFlags);
+  };
+  const __amdgpu_buffer_rsrc_t crs = rsrc(codes + (tile_off >> 2), 1);
+  const __amdgpu_buffer_rsrc_t prs = rsrc(pcodes + (tile_off >> 2), 1);
+  const __amdgpu_buffer_rsrc_t vrs = rsrc((const void*)(float*)(sb + tile_off), 16);
+  const unsigned coff = ok ? threadIdx.x : 0x7fffffffu;
+  uint8_t cq[RING ? NP : D + 1];       // this step's branch codes of planes x .. x + D
+  uint8_t pq[RING ? NP : D + E + 1];   // the previous step's codes of planes x .. x + D + E
+  float4 sq[RING ? NP : D + 1];        // packed Sigma'' of planes x .. x + D
+  unsigned long long oq[RING ? NP : D + 1];   // the ballots that placed them
+  auto req_codes = [&](const __amdgpu_buffer_rsrc_t& rs, unsigned co) -> uint8_t {
+    return __builtin_amdgcn_raw_buffer_load_b8(rs, coff, min(co, clast), 0);
+  };
+  auto req_sigma = [&](unsigned co, unsigned pw, unsigned long long& bal) -> float4 {
+    bal = __builtin_amdgcn_ballot_w64(stored(pw)) & okmask;
     const unsigned slot = __builtin_amdgcn_mbcnt_hi(
         (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-    sv = ld4_nt((sb + pbase(x)) + (segf + 4u * slot));
+    const v4u_t v = __builtin_amdgcn_raw_buffer_load_b128(vrs, segb + 16u * slot,
+                                                          16u * min(co, clast), POL);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
+                       __uint_as_float(v.w));
   };
+  // all first requests before the first wait
   if (nplanes > 0) {
-#pragma unroll
-    for (int i = 0; i < D; ++i) req_codes(i, cq[i]);
     if (!FIRST) {
 #pragma unroll
-      for (int i = 0; i < D + E; ++i) req_pcodes(i, pq[i]);
-#pragma unroll
-      for (int i = 0; i < D; ++i) req_sigma(i, pq[i], sq[i]);
+      for (int i = 0; i < D + E; ++i) pq[i] = req_codes(prs, i * cstride);
     }
+#pragma unroll
+    for (int i = 0; i < D; ++i) cq[i] = req_codes(crs, i * cstride);
   }
+  tau_fetch(0);
+  for (int e = threadIdx.x; e < (R + H) * q4; e += NT) {
+    const int rr = e / q4, c4e = e - rr * q4;
+    const int gr = wrapg(r0 - H + rr, p);
+    const float4 a = ldg4(Cc + (size_t)gr * q + 4 * c4e);
+    const float4 b = FIRST ? make_float4(0.f, 0.f, 0.f, 0.f) : ldg4(Cpc + (size_t)gr * q + 4 * c4e);
+    reinterpret_cast<float4*>(Cs)[e] = a;
+    reinterpret_cast<float4*>(As)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!FIRST) reinterpret_cast<float4*>(Cps)[e] = b;
+  }
+  for (int e = threadIdx.x; e < ER * q4; e += NT) reinterpret_cast<float4*>(Mb)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (!FIRST && nplanes > 0) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) sq[i] = req_sigma(i * cstride, pq[i], oq[i]);
+  }
+  __syncthreads();
+  const float4 cv = ok ? *reinterpret_cast<const float4*>(Cs + (row + H) * q + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float4 cvp =
+      ok && !FIRST ? *reinterpret_cast<const float4*>(Cps + (row + H) * q + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+  // the threads that own the float4s left and right of this one (full rows: wrapped)
+  const int tl = c4 == 0 ? threadIdx.x + q4 - 1 : threadIdx.x - 1;
+  const int tr = c4 + 1 == q4 ? threadIdx.x - q4 + 1 : threadIdx.x + 1;
 
+  unsigned co = 0;                      // code offset of the current plane
   for (int n = 0; n < npairs; ++n) {
     if (n > 0 && (n & 63) == 0) tau_fetch(n);
     const int tpk = __builtin_amdgcn_readlane(tau_lane, n & 63);
     const int2 t = make_int2(tpk >> 16, (int)(short)(tpk & 0xffff));
-    __syncthreads();
-    for (int e = threadIdx.x; e < ER * (ms >> 2); e += NT) reinterpret_cast<float4*>(Mb)[e] = zero4;
-    __syncthreads();
+    // the workgroup's mu' partial of the shift, a thread's first MP4 float4s: requested before
+    // the planes' requests, so that the wait for it at the shift's end waits for none of them
+    gfloat* mpn = mup_tile + (size_t)n * ER * q;
+    const int mp_n4 = ER * q4;
+    constexpr int MP4 = 2;
+    float4 mpv[MP4];
+#pragma unroll
+    for (int u = 0; u < MP4; ++u)
+      mpv[u] = ldg4(mpn + 4 * min((int)threadIdx.x + u * NT, mp_n4 - 1));
     // A' at the item's four pixels, and the previous step's Sigma'' of the items it did not
     // store, -(A'_prev + 0)
     float ab[4], dv[4], gb[4] = {0.f, 0.f, 0.f, 0.f};
     {
-      const float* cr = Cs + (row + H - t.x) * q;
-      const float* crp = Cps + (row + H - t.x) * q;
+      // (lanes past the tile read its first row, unused)
+      const float* cr = Cs + ((ok ? row : 0) + H - t.x) * q;
+      const float* crp = Cps + ((ok ? row : 0) + H - t.x) * q;
       const float ca[4] = {cv.x, cv.y, cv.z, cv.w};
-      const float cap[4] = {cvp.x, cvp.y, cvp.z, cvp.w};
+      const float cap4[4] = {cvp.x, cvp.y, cvp.z, cvp.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         int cc = col + e - t.y;
         cc = cc < 0 ? cc + q : (cc >= q ? cc - q : cc);
-        ab[e] = ok ? 2.f * (ca[e] - cr[cc]) : 0.f;
-        const float abp = ok && !FIRST ? 2.f * (cap[e] - crp[cc]) : 0.f;
+        ab[e] = 2.f * (ca[e] - cr[cc]);
+        const float abp = FIRST ? 0.f : 2.f * (cap4[e] - crp[cc]);
         dv[e] = -(abp + 0.f);
       }
     }
 #pragma unroll
     for (int k1 = -K; k1 <= K; ++k1) {
+      float mw[4 + 2 * K];               // mu' of columns col - K .. col + 3 + K of row + k1
+#pragma unroll
+      for (int i = 0; i < 4 + 2 * K; ++i) mw[i] = 0.f;
 #pragma unroll
       for (int k2 = 0; k2 < KW; ++k2) {
-        const int x = n * NP + (k1 + K) * KW + k2;   // plane of the workgroup
-        req_codes(x + D, cq[D]);
-        if (!FIRST) {
-          req_pcodes(x + D + E, pq[D + E]);
-          req_sigma(x + D, pq[D], sq[D]);
-        }
-        const unsigned cw = ok ? cq[0] : 0u;
-        float b4[4] = {0.f, 0.f, 0.f, 0.f};
-        if (!FIRST) {
-          const bool ps = ok && stored(pq[0]);
-          const float st[4] = {sq[0].x, sq[0].y, sq[0].z, sq[0].w};
+        unsigned cw = 0;
+        float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        bool ps = false;
+        if constexpr (RING) {
+          const int kk = (k1 + K) * KW + k2;   // plane of the shift: known when unrolled
+          if (!FIRST) pq[(kk + D + E) % NP] = req_codes(prs, co + (D + E) * cstride);
+          cq[(kk + D) % NP] = req_codes(crs, co + D * cstride);
+          if (!FIRST) {
+            sq[(kk + D) % NP] = req_sigma(co + D * cstride, pq[(kk + D) % NP], oq[(kk + D) % NP]);
+            s4 = sq[kk];
+            ps = __builtin_amdgcn_inverse_ballot_w64(oq[kk]);
+          }
+          cw = cq[kk];
+        } else {
+          if (!FIRST) pq[D + E] = req_codes(prs, co + (D + E) * cstride);
+          cq[D] = req_codes(crs, co + D * cstride);
+          if (!FIRST) {
+            sq[D] = req_sigma(co + D * cstride, pq[D], oq[D]);
+            s4 = sq[0];
+            ps = __builtin_amdgcn_inverse_ballot_w64(oq[0]);
+          }
+          cw = cq[0];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) b4[e] = ps ? st[e] : dv[e];
-        }
+          for (int i = 0; i < D; ++i) {
+            cq[i] = cq[i + 1];
+            sq[i] = sq[i + 1];
+            oq[i] = oq[i + 1];
+          }
 #pragma unroll
-        for (int i = 0; i < D; ++i) {
-          cq[i] = cq[i + 1];
-          sq[i] = sq[i + 1];
+          for (int i = 0; i < D + E; ++i) pq[i] = pq[i + 1];
         }
-#pragma unroll
-        for (int i = 0; i < D + E; ++i) pq[i] = pq[i + 1];
-        const int o = 4 + (k2 - K);
-        float vb[4], mb[4];
+        const float st[4] = {s4.x, s4.y, s4.z, s4.w};
+        float vb[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const unsigned code = (cw >> (2 * e)) & 3u;
-          const float cbar = -b4[e] - 2.f * ab[e];
-          vb[e] = ab[e] + (code == 0u ? cbar : 0.f);
-          mb[e] = code == 1u ? cbar : (code == 2u ? -cbar : 0.f);
+          const float b4 = FIRST ? 0.f : (ps ? st[e] : dv[e]);
+          const float cbar = -b4 - 2.f * ab[e];
+          // all ones where the branch is >= mu, <= -mu (both: V = 0 with mu = 0)
+          const int hi = (int)(cw << (31 - 2 * e)) >> 31, lo = (int)(cw << (30 - 2 * e)) >> 31;
+          const int cbi = __float_as_int(cbar);
+          vb[e] = ab[e] + __int_as_float(cbi & ~(hi | lo));
+          mw[e + k2] += __int_as_float((cbi & (hi ^ lo)) ^ (lo & (int)0x80000000));
           gb[e] += vb[e];
+          asm volatile("" : "+v"(gb[e]));   // in place: must not sink to the shift's end
         }
-        if (ok) {
-          if (stored(cw)) {
-            // inside the branch the execution mask is the ballot of the storing lanes
-            const unsigned long long bal = __builtin_amdgcn_read_exec();
-            const unsigned slot = __builtin_amdgcn_mbcnt_hi(
-                (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-            st4_nt((sb + tile_off + (size_t)x * kstride) + (segf + 4u * slot),
-                   make_float4(-vb[0], -vb[1], -vb[2], -vb[3]));
+        const unsigned long long bal = __builtin_amdgcn_ballot_w64(stored(cw)) & okmask;
+        if (bal) {
+          // the storing lanes in lane order, then others up to the end of the 64-byte block
+          const unsigned nst = (unsigned)__builtin_popcountll(bal);
+          const unsigned slot = __builtin_amdgcn_mbcnt_hi(
+              (unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+          const unsigned at = co + a0;
+          const unsigned lim = min(((at + nst + 3u) & ~3u) - at, cap);
+          const unsigned to = __builtin_amdgcn_inverse_ballot_w64(bal) ? slot : nst + lane - slot;
+          if (to < lim) {
+            const v4u_t w = {__float_as_uint(-vb[0]), __float_as_uint(-vb[1]),
+                             __float_as_uint(-vb[2]), __float_as_uint(-vb[3])};
+            __builtin_amdgcn_raw_buffer_store_b128(w, vrs, segb + 16u * to, 16u * co, POL);
           }
-          float* mrow = Mb + (row + K + k1) * ms + col + o;   // mu' at (row + k1, col + k2 - K + e)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) mrow[e] += mb[e];
         }
-        __syncthreads();   // j -> j + k is one-to-one for a fixed k; k's overlap
+        co += cstride;
+      }
+      // fold the patch row into the tile: what reaches beyond the thread's columns goes to its
+      // neighbours through Eg (two copies in turn, so that one barrier per patch row does)
+      float* eg = Eg + ((k1 + K) & 1) * 2 * K * NT;
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        eg[i * NT + threadIdx.x] = mw[i];                    // columns col - K + i
+        eg[(K + i) * NT + threadIdx.x] = mw[4 + K + i];      // columns col + 4 + i
+      }
+      __syncthreads();                   // also: the rows of the patch row before are folded
+      if (ok) {
+        float v[4] = {mw[K], mw[K + 1], mw[K + 2], mw[K + 3]};
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          v[i] += eg[(K + i) * NT + tl];                     // the left neighbour's right reach
+          v[4 - K + i] += eg[i * NT + tr];                   // the right neighbour's left reach
+        }
+        float4* mrow = reinterpret_cast<float4*>(Mb + (row + K + k1) * q + col);
+        const float4 m = *mrow;
+        *mrow = make_float4(m.x + v[0], m.y + v[1], m.z + v[2], m.w + v[3]);
       }
     }
     if (ok) {
@@ -283,41 +361,21 @@ sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ item
       }
     }
     __syncthreads();
-    // fold the padded columns into their wrapped positions and accumulate the partial tile,
-    // as float4s, a thread's first MP4 read before one wait: a row of Mb holds PADW = 4
-    // columns on either side, one float4 folded into the row's first and last float4
-    gfloat* mpn = mup_tile + (size_t)n * ER * q;
-    const int mp_n4 = ER * q4;
-    auto folded = [&](int e4) {
-      const int rr = e4 / q4, c4 = e4 - rr * q4;
-      const float4* mrow = reinterpret_cast<const float4*>(Mb + rr * ms);
-      float4 v = mrow[1 + c4];
-      if (c4 == 0) {                               // columns q .. q + 3
-        const float4 w = mrow[1 + q4];
-        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
-      }
-      if (c4 == q4 - 1) {                          // columns -4 .. -1
-        const float4 w = mrow[0];
-        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
-      }
-      return v;
-    };
-    constexpr int MP4 = 2;
-    float4 mpv[MP4];
-#pragma unroll
-    for (int u = 0; u < MP4; ++u)
-      mpv[u] = ldg4(mpn + 4 * min((int)threadIdx.x + u * NT, mp_n4 - 1));
+    // accumulate the tile into the workgroup's partial and clear it (the next shift adds to it
+    // behind a barrier)
 #pragma unroll
     for (int u = 0; u < MP4; ++u) {
       const int e4 = threadIdx.x + u * NT;
       if (e4 < mp_n4) {
-        const float4 v = folded(e4);
+        const float4 v = reinterpret_cast<const float4*>(Mb)[e4];
+        reinterpret_cast<float4*>(Mb)[e4] = make_float4(0.f, 0.f, 0.f, 0.f);
         stg4(mpn + 4 * e4, make_float4(mpv[u].x + v.x, mpv[u].y + v.y, mpv[u].z + v.z,
                                        mpv[u].w + v.w));
       }
     }
     for (int e4 = threadIdx.x + MP4 * NT; e4 < mp_n4; e4 += NT) {
-      const float4 v = folded(e4), m = ldg4(mpn + 4 * e4);
+      const float4 v = reinterpret_cast<const float4*>(Mb)[e4], m = ldg4(mpn + 4 * e4);
+      reinterpret_cast<float4*>(Mb)[e4] = make_float4(0.f, 0.f, 0.f, 0.f);
       stg4(mpn + 4 * e4, make_float4(m.x + v.x, m.y + v.y, m.z + v.z, m.w + v.w));
     }
   }
@@ -805,14 +863,15 @@ int launch_kind(const Batch& B, Kind kind, const char* name, Kern kern, hipStrea
   return NLPR_OK;
 }
 
-template <int K>
-int launch_sbwd(const Batch& B, const Group& g, size_t lds, int cb, const uint8_t* codes, int sb,
-                int xr, int halo, int mup, const uint8_t* pcodes, int cbp, hipStream_t s) {
+template <int K, bool CACHED>
+int launch_sbwd_policy(const Batch& B, const Group& g, size_t lds, int cb, const uint8_t* codes,
+                       int sb, int xr, int halo, int mup, const uint8_t* pcodes, int cbp,
+                       hipStream_t s) {
   if (pcodes) {
-    hipLaunchKernelGGL((sweep_bwd_kernel<K, false>), dim3(g.nitems), dim3(256), lds, s,
+    hipLaunchKernelGGL((sweep_bwd_kernel<K, false, CACHED>), dim3(g.nitems), dim3(256), lds, s,
                        B.d_desc, g.d_items, cb, codes, sb, xr, halo, mup, pcodes, cbp);
   } else {
-    hipLaunchKernelGGL((sweep_bwd_kernel<K, true>), dim3(g.nitems), dim3(256), lds, s,
+    hipLaunchKernelGGL((sweep_bwd_kernel<K, true, CACHED>), dim3(g.nitems), dim3(256), lds, s,
                        B.d_desc, g.d_items, cb, codes, sb, xr, halo, mup, codes, cb);
   }
   NLPR_LAUNCH_CHECK("sweep_bwd_kernel");
@@ -820,11 +879,22 @@ int launch_sbwd(const Batch& B, const Group& g, size_t lds, int cb, const uint8_
 }
 
 template <int K>
+int launch_sbwd(const Batch& B, const Group& g, size_t lds, int cb, const uint8_t* codes, int sb,
+                int xr, int halo, int mup, const uint8_t* pcodes, int cbp, hipStream_t s) {
+  return g.policy == kSweepCached
+             ? launch_sbwd_policy<K, true>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s)
+             : launch_sbwd_policy<K, false>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s);
+}
+
+template <int K>
 int sbwd_attr() {
-  NLPR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_bwd_kernel<K, true>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxSweepLds));
-  NLPR_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_bwd_kernel<K, false>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxSweepLds));
+  const void* kern[4] = {reinterpret_cast<const void*>(sweep_bwd_kernel<K, true, true>),
+                         reinterpret_cast<const void*>(sweep_bwd_kernel<K, true, false>),
+                         reinterpret_cast<const void*>(sweep_bwd_kernel<K, false, true>),
+                         reinterpret_cast<const void*>(sweep_bwd_kernel<K, false, false>)};
+  for (const void* k : kern)
+    NLPR_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)kMaxSweepLds));
   return NLPR_OK;
 }
 
@@ -832,7 +902,7 @@ int sbwd_attr() {
 
 size_t sweep_bwd_lds(const Plan& P) {
   const int R = P.sweep.rows, H = P.sweep.halo, K = P.prm.K, q = P.prm.q;
-  return (size_t)((R + 2 * K) * (q + 2 * PADW) + 3 * (R + H) * q) * sizeof(float);
+  return (size_t)((R + 2 * K) * q + 3 * (R + H) * q + 4 * K * 256) * sizeof(float);
 }
 size_t weights_bwd_lds(const Plan& P) {
   const int K = P.prm.K;

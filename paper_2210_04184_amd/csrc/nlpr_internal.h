@@ -253,6 +253,11 @@ typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v2f_t gv2f;
 typedef __attribute__((address_space(1))) v4f_t gv4f;
 typedef __attribute__((address_space(1))) v2i_t gv2i;
+// cache policy of a buffer access: non-temporal
+constexpr int kCacheNT = 2;
+// last word of a raw byte-addressed buffer resource: 32-bit data format (bits 15-18 = 4),
+// no stride, no swizzle; offsets are bytes from the base
+constexpr int kRawBufferFlags = 0x00020000;
 __device__ __forceinline__ const gfloat* as_global(const float* p) { return (const gfloat*)p; }
 __device__ __forceinline__ gfloat* as_global(float* p) { return (gfloat*)p; }
 template <typename G>

@@ -43,11 +43,6 @@ namespace {
 #ifndef NLPR_SWEEP_NT
 #define NLPR_SWEEP_NT 1
 #endif
-// cache policy of a buffer access: non-temporal
-constexpr int kCacheNT = 2;
-// last word of a raw byte-addressed buffer resource: 32-bit data format (bits 15-18 = 4),
-// no stride, no swizzle; offsets are bytes from the base
-constexpr int kRawBufferFlags = 0x00020000;
 __device__ __forceinline__ float4 ld_nt(const gfloat* p) {
 #if NLPR_SWEEP_NT
   const v4f_t v = __builtin_nontemporal_load((const gv4f*)p);
@@ -478,10 +473,6 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
             vv[e] = v;
             acc[e] = __builtin_fmaf(-2.f, cl, v);
             nv[e] = cl;
-            if (CODES) {
-              const unsigned bc = fabsf(v) < mu4[e] ? 0u : (v > 0.f ? 1u : (v < 0.f ? 2u : 3u));
-              branch |= bc << (2 * e);
-            }
           }
           // the code byte, shifted in one bit at a time (alignbit(c, x, 31) = c << 1 | x >> 31):
           // the off flags (sign bits of |V| - mu) of elements 3..0, then the signs of V
@@ -491,6 +482,25 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
 #pragma unroll
           for (int e = 3; e >= 0; --e)
             code = __builtin_amdgcn_alignbit(code, __float_as_uint(vv[e]), 31);
+          if (CODES) {
+            // the branches from the code byte: on the threshold with the sign clear (1) or set
+            // (2), bits e spread to bits 2e; a wave with a V that has no sign (0 or NaN) takes
+            // them from the comparisons
+            unsigned w = (~code >> 4 & ~code & 15u) | (~code >> 4 & code & 15u) << 16;
+            w = (w | w << 2) & 0x00330033u;
+            w = (w | w << 1) & 0x00550055u;
+            branch = w | w >> 15;
+            bool odd = false;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd |= !(fabsf(vv[e]) > 0.f);
+            if (__builtin_amdgcn_ballot_w64(odd)) {
+              branch = 0;
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                branch |= (fabsf(vv[e]) < mu4[e] ? 0u : (vv[e] > 0.f ? 1u : (vv[e] < 0.f ? 2u : 3u)))
+                          << (2 * e);
+            }
+          }
           A[m].x += acc[0];   // lanes past the tile too: they never use it
           A[m].y += acc[1];
           A[m].z += acc[2];

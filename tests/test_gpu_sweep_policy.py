@@ -65,3 +65,32 @@ def test_packed_runs_stay_in_their_segments(kw):
         thr = torch.roll(mu, (K - k // (2 * K + 1), K - k % (2 * K + 1)), (-2, -1))
         assert bool((sig[:, k].abs() <= thr[:, None]).all())
     assert np.isfinite(Z.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("K,Sw,filler", [(1, 2, 340), (0, 2, 3100), (2, 1, 360)])
+def test_policy_does_not_change_the_gradient(K, Sw, filler):
+    """Bands that R does not see are independent of the others: with `filler` such bands, all
+    zero, Z and every gradient of the first two (one pair of the X-update) must be those of the
+    scene without them, bit for bit, although the larger state runs streamed and the small one
+    cached.  (The zero bands also take the branch records through V = 0.)"""
+    p, q, d, T = 48, 64, 4, 4
+    sc = synth.make_scene(synth.small_spec(p=p, q=q, L=2, Lh=1, d=d, blur_radius=2, K=K, Sw=Sw,
+                                           iters=T, seed=8))
+    Yh = torch.from_numpy(sc.Yh).cuda()
+    dZ = torch.from_numpy(np.random.default_rng(2).standard_normal((2, p, q)).astype(np.float32))
+    res = []
+    for L in (90, 90 + filler):       # both with a whole tile per sweep workgroup
+        R = np.zeros((L, 1), np.float32)
+        R[0] = sc.R[0, 0]
+        plan = nlpr.Plan(p, q, L, 1, d, sc.blur, R, K, Sw, T, sc.spec.lam, sc.spec.rho, sc.h)
+        assert (plan.info().sigma_elems * 4 > 384 << 20) == (L > 90)
+        Yl = torch.zeros((L, p // d, q // d), device="cuda")
+        Yl[:2] = torch.from_numpy(sc.Yl).cuda()
+        Z, ws, ck = plan.forward(Yl, Yh)
+        full = torch.zeros((L, p, q), device="cuda")
+        full[:2] = dZ.cuda()
+        dYl, dYh, ds = plan.backward(Yl, Yh, full, ws, ck)
+        assert not bool(dYl[2:].any())
+        res.append((Z[:2], dYl[:2], dYh, ds))
+    for a, b in zip(*res):
+        assert torch.equal(a, b)

@@ -75,7 +75,7 @@ __global__ void den_kernel(float* invden, int p, int q, const float* blur, int r
 // matrix is diag(a) plus a rank-one term, so Sherman-Morrison gives
 //   x_j = c_j / a_j - (conj(b^_j) / a_j) gamma sum_k (b^_k / a_k) c_k,
 //   gamma = 1 / (rho d^2 + sum_k |b^_k|^2 / a_k).
-// One thread per group, all in FP64; stored FP32 in column-major [q][p] order with the
+// One thread per group, all in FP64; stored FP32 in [p][q] order with the
 // 1/(p q) of the unnormalised inverse DFT folded into ia and v:
 //   ia = 1 / (a p q),  u = b^ / a,  v = gamma conj(b^) / (a p q).
 __device__ void freq_terms(int u, int v, int p, int q, const float* blur, int r, const int2* taus,
@@ -126,7 +126,7 @@ __global__ void fused_tables_kernel(int p, int q, int d, const float* blur, int 
       const int u = w1 + m1 * pd, v = w2 + m2 * qd;
       double br, bi, a;
       freq_terms(u, v, p, q, blur, r, taus, npairs, npatch, &br, &bi, &a);
-      const size_t o = (size_t)v * p + u;
+      const size_t o = (size_t)u * q + v;
       ia[o] = (float)(1.0 / (a * pq));
       fu[o] = make_float2((float)(br / a), (float)(bi / a));
       fv[o] = make_float2((float)(gamma * br / (a * pq)), (float)(-gamma * bi / (a * pq)));

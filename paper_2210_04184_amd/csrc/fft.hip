@@ -13,10 +13,19 @@
 //   rows_inv   : inverse DFT along rows, unpack the two bands
 // Every pass runs over a batch of scenes (see nlpr_internal.h); lines per block and columns
 // per block are picked per image size by timing candidates when a plan is created.
-// Each 1-D transform is a Stockham autosort FFT (mixed radix 2/3/4/8) staged in LDS:
-// every stage reads R values strided by n/R, twiddles them, does an R-point DFT and writes
-// them to their natural-order position, so no bit reversal is needed.  Twiddles come from
+// Each 1-D transform is a Stockham autosort FFT (mixed radix 2/3/4/8): every stage reads R
+// values strided by n/R, twiddles them, does an R-point DFT and writes them to their
+// natural-order position, so no bit reversal is needed.  The first stage reads global memory
+// and the last one writes it (both touch points n/R apart per thread, neighbouring threads
+// neighbouring points), so LDS only carries the exchanges between stages.  Twiddles come from
 // a table computed in FP64.
+//
+// The passes are bound by the latency of their requests and barriers (8 MB planes live in the
+// caches).  Per launch at 256 x 256 x 31 / 1024 x 1024 x 4, against passes that staged every
+// line through LDS on the way in and out, with two block barriers per stage: rows 9.3 -> 7.3 /
+// 15.1 -> 11.9 us, columns 17.0 -> 13.7 / 39 -> 20 us (half of that from the order of the
+// workgroups); columns of fused-S at 192 x 256 x 31, whose groups one thread each solved:
+// 29 -> 17 us; 12-scene batch: rows 24.6 -> 13.5, columns 38 -> 27 us.
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -95,13 +104,16 @@ template <bool INV> struct Dft<3, INV> {
   }
 };
 
-// One Stockham stage of radix R on a line of n points in LDS.  Ns is the product of the
-// radices of the earlier stages; tw holds the line's n twiddles, staged in LDS.  Threads
-// t < tpl of the line take part; tpl >= ceil(n/8) keeps every thread at <= ceil(8/R)
-// butterflies.  All threads of the block must call it.
-template <int R, bool INV>
-__device__ __forceinline__ void fft_stage(float2* buf, int n, int Ns, const float2* tw, int t,
-                                          int tpl) {
+// One Stockham stage of radix R on a line of n points.  Ns is the product of the radices of
+// the earlier stages; tw holds the line's n twiddles, staged in LDS.  Threads t < tpl of the
+// line take part; tpl >= ceil(n/8) keeps every thread at <= ceil(8/R) butterflies.
+// rd(u, r, i) gives point i, wr(u, r, i, v) takes it (butterfly u of the thread, leg r).
+// IN_LDS / OUT_LDS: rd reads / wr writes the line's LDS buffer; between a read and a write of
+// it, and after a write, sync() orders the threads of a line.  Every thread of the block
+// calls it.
+template <int R, bool INV, bool IN_LDS, bool OUT_LDS, class RD, class WR, class SYNC>
+__device__ __forceinline__ void fft_stage(int n, int Ns, int step, const float2* tw, int t,
+                                          int tpl, RD rd, WR wr, SYNC sync) {
   constexpr int MAXB = (8 + R - 1) / R;
   const int nb = n / R;
   float2 v[MAXB][R];
@@ -110,51 +122,93 @@ __device__ __forceinline__ void fft_stage(float2* buf, int n, int Ns, const floa
     const int j = t + u * tpl;
     if (t < tpl && j < nb) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[u][r] = buf[j + r * nb];
+      for (int r = 0; r < R; ++r) v[u][r] = rd(u, r, j + r * nb);
     }
   }
-  __syncthreads();
-  const int step = n / (Ns * R);
+  if (IN_LDS && OUT_LDS) sync();
 #pragma unroll
   for (int u = 0; u < MAXB; ++u) {
     const int j = t + u * tpl;
     if (t < tpl && j < nb) {
-      const int k = j % Ns;
+      const int k = (Ns & (Ns - 1)) == 0 ? j & (Ns - 1) : j % Ns;
+      if constexpr (IN_LDS) {            // the twiddles of a transform's first stage are 1
 #pragma unroll
-      for (int r = 1; r < R; ++r) {
-        float2 w = tw[r * k * step];
-        if (INV) w.y = -w.y;
-        v[u][r] = cmul(v[u][r], w);
+        for (int r = 1; r < R; ++r) {
+          float2 w = tw[r * k * step];
+          if (INV) w.y = -w.y;
+          v[u][r] = cmul(v[u][r], w);
+        }
       }
       Dft<R, INV>::run(v[u]);
+      // the values as they are here: a part computed in a branch of wr would round other
+      // products into its additions
+      if constexpr (!OUT_LDS) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) asm volatile("" : "+v"(v[u][r].x), "+v"(v[u][r].y));
+      }
       const int base = (j - k) * R + k;
 #pragma unroll
-      for (int r = 0; r < R; ++r) buf[base + r * Ns] = v[u][r];
+      for (int r = 0; r < R; ++r) wr(u, r, base + r * Ns, v[u][r]);
     }
   }
-  __syncthreads();
+  if (OUT_LDS) sync();
 }
 
-// Twiddles of a line length, copied from the FP64-computed table to LDS (before the
-// barrier that follows the data load) so the stages read them without global latency.
+template <bool INV, bool IN_LDS, bool OUT_LDS, class RD, class WR, class SYNC>
+__device__ __forceinline__ void fft_stage_r(int R, int n, int Ns, int step, const float2* tw,
+                                            int t, int tpl, RD rd, WR wr, SYNC sync) {
+  if (R == 8) fft_stage<8, INV, IN_LDS, OUT_LDS>(n, Ns, step, tw, t, tpl, rd, wr, sync);
+  else if (R == 4) fft_stage<4, INV, IN_LDS, OUT_LDS>(n, Ns, step, tw, t, tpl, rd, wr, sync);
+  else if (R == 2) fft_stage<2, INV, IN_LDS, OUT_LDS>(n, Ns, step, tw, t, tpl, rd, wr, sync);
+  else fft_stage<3, INV, IN_LDS, OUT_LDS>(n, Ns, step, tw, t, tpl, rd, wr, sync);
+}
+
+// Twiddles of a line length, copied from the FP64-computed table to LDS, so that the stages
+// read them without global latency (a barrier follows before the second stage).
 __device__ __forceinline__ void stage_twiddles(float2* twl, const LineFFT& f) {
   const gfloat* tw = (const gfloat*)f.tw;
   for (int e = threadIdx.x; e < f.n; e += blockDim.x) twl[e] = ldg2(tw + 2 * e);
 }
 
-template <bool INV>
-__device__ __forceinline__ void fft_line(float2* buf, const LineFFT& f, int t, int tpl,
-                                         const float2* tw) {
-  int Ns = 1;
-  for (int s = 0; s < f.nfac; ++s) {
+// A line transform from `first` (points of global memory) to `last`, through the line's LDS
+// buffer (brd, bwr).  sync() orders the threads of a line, and its first call also orders the
+// staged twiddles, so it is made a block barrier by the caller (sync0).  Transforms of one
+// stage (n = 8) exchange nothing.
+template <bool INV, class RD, class WR, class BR, class BW, class SYNC0, class SYNC>
+__device__ __forceinline__ void fft_line(const LineFFT& f, int t, int tpl, const float2* tw,
+                                         RD first, WR last, BR brd, BW bwr, SYNC0 sync0,
+                                         SYNC sync) {
+  const int nf = f.nfac;
+  if (nf == 1) {                         // n = 8: the only length of one factor
+    fft_stage<8, INV, false, false>(8, 1, 1, tw, t, tpl, first, last, sync);
+    return;
+  }
+  int Ns = f.fac[0], step = f.n / f.fac[0];
+  fft_stage_r<INV, false, true>(f.fac[0], f.n, 1, step, tw, t, tpl, first, bwr, sync0);
+  for (int s = 1; s < nf - 1; ++s) {
     const int R = f.fac[s];
-    if (R == 8) fft_stage<8, INV>(buf, f.n, Ns, tw, t, tpl);
-    else if (R == 4) fft_stage<4, INV>(buf, f.n, Ns, tw, t, tpl);
-    else if (R == 2) fft_stage<2, INV>(buf, f.n, Ns, tw, t, tpl);
-    else fft_stage<3, INV>(buf, f.n, Ns, tw, t, tpl);
+    step /= R;
+    fft_stage_r<INV, true, true>(R, f.n, Ns, step, tw, t, tpl, brd, bwr, sync);
     Ns *= R;
   }
+  fft_stage_r<INV, true, false>(f.fac[nf - 1], f.n, Ns, 1, tw, t, tpl, brd, last, sync);
 }
+
+// Order the LDS accesses of a line's threads.  Where they are lanes of one wave (tpl divides
+// 64) the LDS pipe does it, since a wave's accesses execute in order: only the compiler has to
+// keep them in place.  Else a block barrier.
+__device__ __forceinline__ void line_sync(bool in_wave) {
+  if (in_wave) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
+// LDS position of point i of a row line: one point of padding per 8, so that the stages'
+// stores, 8 points apart at first, spread over the banks.
+__device__ __forceinline__ int row_pos(int i) { return i + (i >> 3); }
 
 // Pack bands (2m, 2m+1) of C, forward DFT along rows.  Local block = (pair, row block).
 __global__ void fft_rows_fwd(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
@@ -166,61 +220,137 @@ __global__ void fft_rows_fwd(const SceneDesc* __restrict__ sd, const int2* __res
   const int nrb = ceil_div(p, lpb);
   const int m = it.y / nrb, row0 = (it.y - m * nrb) * lpb;
   const size_t plane = (size_t)p * q;
-  const gfloat* C = gslot<const gfloat>(S, c_s);
-  float2* twl = sh + lpb * q;
-  stage_twiddles(twl, S.fq);
-  const gfloat* Ca = C + (size_t)(2 * m) * plane;
-  const gfloat* Cb = (2 * m + 1 < L) ? C + (size_t)(2 * m + 1) * plane : nullptr;
-  // 16-byte loads (4 points of a row; q % 4 == 0) when the buffer allows, else 4-byte ones
-  if ((reinterpret_cast<uintptr_t>(C) & 15) == 0) {
-    const int q4 = q >> 2;
-    for (int e = threadIdx.x; e < lpb * q4; e += blockDim.x) {
-      const int l = e / q4, i4 = e - l * q4, r = row0 + l;
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-      if (r < p) {
-        a = ldg4(Ca + (size_t)r * q + 4 * i4);
-        if (Cb) b = ldg4(Cb + (size_t)r * q + 4 * i4);
-      }
-      float2* d = sh + l * q + 4 * i4;
-      d[0] = make_float2(a.x, b.x);
-      d[1] = make_float2(a.y, b.y);
-      d[2] = make_float2(a.z, b.z);
-      d[3] = make_float2(a.w, b.w);
-    }
-  } else {
-    for (int e = threadIdx.x; e < lpb * q; e += blockDim.x) {
-      const int l = e / q, i = e - l * q, r = row0 + l;
-      float2 v = make_float2(0.f, 0.f);
-      if (r < p) {
-        v.x = Ca[(size_t)r * q + i];
-        if (Cb) v.y = Cb[(size_t)r * q + i];
-      }
-      sh[e] = v;
-    }
-  }
-  __syncthreads();
-  const int g = threadIdx.x / tpl;
-  const int t = (g < lpb) ? threadIdx.x - g * tpl : tpl;
-  fft_line<false>(sh + (g < lpb ? g : 0) * q, S.fq, t, tpl, twl);
+  const int g = threadIdx.x / tpl, r = row0 + g;
+  const bool act = g < lpb && r < p;
+  const int t = act ? threadIdx.x - g * tpl : tpl;
+  const bool two = 2 * m + 1 < L;
+  const gfloat* Ca = gslot<const gfloat>(S, c_s) + (size_t)(2 * m) * plane;
+  const gfloat* Cb = Ca + (two ? plane : 0);
   gfloat* Fm = gslot<gfloat>(S, f_s) + 2 * (size_t)m * plane;   // complex, interleaved
-  const int q2 = q >> 1;                // two complex points per 16-byte store
-  for (int e = threadIdx.x; e < lpb * q2; e += blockDim.x) {
-    const int l = e / q2, i2 = e - l * q2, r = row0 + l;
-    if (r < p) {
-      const float2 u = sh[l * q + 2 * i2], w = sh[l * q + 2 * i2 + 1];
-      stg4(Fm + 2 * ((size_t)r * q + 2 * i2), make_float4(u.x, u.y, w.x, w.y));
-    }
-  }
+  const unsigned ro = (unsigned)r * q;
+  float2* buf = sh + (act ? g : 0) * row_pos(q);
+  float2* twl = sh + lpb * row_pos(q);
+  stage_twiddles(twl, S.fq);
+  const bool in_wave = 64 % tpl == 0;
+  fft_line<false>(
+      S.fq, t, tpl, twl,
+      [&](int, int, int i) { return make_float2(Ca[ro + i], two ? Cb[ro + i] : 0.f); },
+      [&](int, int, int i, float2 v) { stg2(Fm + 2 * (ro + i), v); },
+      [&](int, int, int i) { return buf[row_pos(i)]; },
+      [&](int, int, int i, float2 v) { buf[row_pos(i)] = v; }, [] { __syncthreads(); },
+      [&] { line_sync(in_wave); });
 }
 
 // Forward DFT along columns, multiply by invden, inverse DFT along columns.
-// Local block = (pair, column block); LDS holds cb columns of p points.
+// Local block = (pair, column block); LDS holds cb columns of p points, point i of column l at
+// i cb + l.  Thread = (column l, thread t of the line), columns fastest: a stage's accesses to
+// global memory and to LDS are runs of cb neighbouring columns.  The weights 1/den of the
+// thread's last-stage points are requested before the forward transform.  At a power of 2 the
+// last forward stage leaves a thread the points its first inverse stage reads (p = 8 tpl, first
+// radix 8, last 8, 4 or 2): they stay in registers.
 //
 // Fused-S scenes solve, per aliasing group of d^2 frequencies, the system of
 // fused_tables_kernel instead of the division: line l of the block holds column
 // b0 + (l % cbb) + (l / cbb) q/d (cbb = cb / d base columns and their d - 1 column aliases),
 // so each group's d^2 entries (rows i1 + m1 p/d of those d columns) are in LDS.  All lines
-// are transformed forward, the group solves run, then all lines are transformed back.
+// are transformed forward, the group solves run, then all lines are transformed back.  A group
+// is solved by d threads, one per column: each sums the d entries of its column, the d sums
+// are added through LDS in the order of the columns, and each thread updates its d entries.
+template <int RL>
+__device__ __forceinline__ void cols_plain(const SceneDesc& S, int t, int tpl, int cb, int l,
+                                           int col, float2* sh, const float2* twl, gfloat* Fm) {
+  const int p = S.p, q = S.q, nf = S.fp.nfac;
+  constexpr int MAXB = (8 + RL - 1) / RL;
+  constexpr bool KEEP = RL != 3;         // with p = 8 tpl, checked by the caller's choice of RL
+  const gfloat* invden = as_global(S.invden);
+  const int nb = p / RL;
+  auto brd = [&](int, int, int i) { return sh[i * cb + l]; };
+  auto bwr = [&](int, int, int i, float2 v) { sh[i * cb + l] = v; };
+  auto sync = [] { __syncthreads(); };
+  auto gin = [&](int, int, int i) { return ldg2(Fm + 2 * (unsigned)(i * q + col)); };
+  auto gout = [&](int, int, int i, float2 v) { stg2(Fm + 2 * (unsigned)(i * q + col), v); };
+  // the points of the last forward stage: i = t + u tpl + r nb
+  float sv[MAXB][RL];
+#pragma unroll
+  for (int u = 0; u < MAXB; ++u)
+#pragma unroll
+    for (int r = 0; r < RL; ++r)
+      sv[u][r] = t < tpl && t + u * tpl < nb ? invden[(unsigned)((t + u * tpl + r * nb) * q + col)] : 0.f;
+  float2 keep[KEEP ? 8 : 1];
+  auto scaled = [&](int u, int r, int i, float2 v) {
+    v = cscale(v, sv[u][r]);
+    if constexpr (KEEP) keep[u + MAXB * r] = v;    // point t + (u + MAXB r) tpl
+    else bwr(u, r, i, v);
+  };
+  // forward
+  const int R0 = S.fp.fac[0];
+  int Ns = R0, step = p / R0;
+  if (nf == 1) {                         // p = 8
+    fft_stage<RL, false, false, !KEEP>(p, 1, 1, twl, t, tpl, gin, scaled, sync);
+  } else {
+    fft_stage_r<false, false, true>(R0, p, 1, step, twl, t, tpl, gin, bwr, sync);
+    for (int s = 1; s < nf - 1; ++s) {
+      const int R = S.fp.fac[s];
+      step /= R;
+      fft_stage_r<false, true, true>(R, p, Ns, step, twl, t, tpl, brd, bwr, sync);
+      Ns *= R;
+    }
+    fft_stage<RL, false, true, !KEEP>(p, Ns, 1, twl, t, tpl, brd, scaled, sync);
+    if (KEEP) sync();                    // the last reads of the buffer before it is rewritten
+  }
+  // inverse
+  if constexpr (KEEP) {
+    auto kin = [&](int, int r, int) { return keep[r]; };
+    if (nf == 1) {
+      fft_stage<8, true, false, false>(p, 1, 1, twl, t, tpl, kin, gout, sync);
+      return;
+    }
+    fft_stage<8, true, false, true>(p, 1, p / 8, twl, t, tpl, kin, bwr, sync);
+  } else {
+    fft_stage_r<true, true, true>(R0, p, 1, p / R0, twl, t, tpl, brd, bwr, sync);
+  }
+  Ns = R0;
+  step = p / R0;
+  for (int s = 1; s < nf - 1; ++s) {
+    const int R = S.fp.fac[s];
+    step /= R;
+    fft_stage_r<true, true, true>(R, p, Ns, step, twl, t, tpl, brd, bwr, sync);
+    Ns *= R;
+  }
+  fft_stage_r<true, true, false>(S.fp.fac[nf - 1], p, Ns, 1, twl, t, tpl, brd, gout, sync);
+}
+
+
+// The forward transform of a line into its LDS buffer, and the inverse one out of it.
+template <class RD, class BR, class BW, class SYNC>
+__device__ __forceinline__ void cols_to_lds(const SceneDesc& S, int t, int tpl,
+                                            const float2* twl, RD gin, BR brd, BW bwr,
+                                            SYNC sync) {
+  const int p = S.p, nf = S.fp.nfac, R0 = S.fp.fac[0];
+  int Ns = R0, step = p / R0;
+  fft_stage_r<false, false, true>(R0, p, 1, step, twl, t, tpl, gin, bwr, sync);
+  for (int s = 1; s < nf; ++s) {
+    const int R = S.fp.fac[s];
+    step /= R;
+    fft_stage_r<false, true, true>(R, p, Ns, step, twl, t, tpl, brd, bwr, sync);
+    Ns *= R;
+  }
+}
+template <class BR, class BW, class WR, class SYNC>
+__device__ __forceinline__ void cols_from_lds(const SceneDesc& S, int t, int tpl,
+                                              const float2* twl, BR brd, BW bwr, WR gout,
+                                              SYNC sync) {
+  const int p = S.p, nf = S.fp.nfac;
+  int Ns = 1, step = p;
+  for (int s = 0; s < nf - 1; ++s) {
+    const int R = S.fp.fac[s];
+    step /= R;
+    fft_stage_r<true, true, true>(R, p, Ns, step, twl, t, tpl, brd, bwr, sync);
+    Ns *= R;
+  }
+  fft_stage_r<true, true, false>(S.fp.fac[nf - 1], p, Ns, 1, twl, t, tpl, brd, gout, sync);
+}
+
 __global__ void fft_cols_solve(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
                                int f_s) {
   extern __shared__ float2 sh[];
@@ -233,133 +363,78 @@ __global__ void fft_cols_solve(const SceneDesc* __restrict__ sd, const int2* __r
   gfloat* Fm = gslot<gfloat>(S, f_s) + 2 * (size_t)m * plane;   // complex, interleaved
   float2* twl = sh + cb * p;
   stage_twiddles(twl, S.fp);
+  const int t0 = threadIdx.x / cb, l = threadIdx.x - t0 * cb;
   const int d = S.d, cbb = S.fused ? cb / d : cb, qd = q / d;
-  // column of LDS line l (-1: past the image)
-  auto column = [&](int l) -> int {
-    if (!S.fused) {
-      const int col = cblk * cb + l;
-      return col < q ? col : -1;
-    }
-    const int bc = cblk * cbb + l % cbb;
-    return bc < qd ? bc + (l / cbb) * qd : -1;
-  };
-  // plain layout with an even block width: two neighbouring columns per 16-byte access
-  const bool pairs = !S.fused && (cb & 1) == 0;
-  if (pairs) {
-    const int cb2 = cb >> 1;
-    for (int e = threadIdx.x; e < cb2 * p; e += blockDim.x) {
-      const int i = e / cb2, l = 2 * (e - i * cb2), col = cblk * cb + l;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (col + 1 < q) {
-        v = ldg4(Fm + 2 * ((size_t)i * q + col));
-      } else if (col < q) {
-        const float2 u = ldg2(Fm + 2 * ((size_t)i * q + col));
-        v.x = u.x;
-        v.y = u.y;
-      }
-      sh[l * p + i] = make_float2(v.x, v.y);
-      sh[(l + 1) * p + i] = make_float2(v.z, v.w);
-    }
+  // column of line l (-1: past the image)
+  int col;
+  if (!S.fused) {
+    col = cblk * cb + l;
+    if (col >= q) col = -1;
   } else {
-    for (int e = threadIdx.x; e < cb * p; e += blockDim.x) {
-      const int i = e / cb, l = e - i * cb, col = column(l);
-      sh[l * p + i] = (col >= 0) ? ldg2(Fm + 2 * ((size_t)i * q + col)) : make_float2(0.f, 0.f);
+    const int bc = cblk * cbb + l % cbb;
+    col = bc < qd ? bc + (l / cbb) * qd : -1;
+  }
+  const int t = t0 < tpl && col >= 0 ? t0 : tpl;
+  if (!S.fused) {
+    // (a length with a factor 3 ends on radix 3; the others are powers of 2, p = 8 tpl, and
+    // start on radix 8)
+    const int RL = S.fp.fac[S.fp.nfac - 1];
+    if (RL == 3) cols_plain<3>(S, t, tpl, cb, l, col, sh, twl, Fm);
+    else if (RL == 8) cols_plain<8>(S, t, tpl, cb, l, col, sh, twl, Fm);
+    else if (RL == 4) cols_plain<4>(S, t, tpl, cb, l, col, sh, twl, Fm);
+    else cols_plain<2>(S, t, tpl, cb, l, col, sh, twl, Fm);
+    return;
+  }
+  auto brd = [&](int, int, int i) { return sh[i * cb + l]; };
+  auto bwr = [&](int, int, int i, float2 v) { sh[i * cb + l] = v; };
+  auto gin = [&](int, int, int i) { return ldg2(Fm + 2 * (unsigned)(i * q + col)); };
+  auto gout = [&](int, int, int i, float2 v) { stg2(Fm + 2 * (unsigned)(i * q + col), v); };
+  auto sync = [] { __syncthreads(); };
+  cols_to_lds(S, t, tpl, twl, gin, brd, bwr, sync);
+  const int pd = p / d;
+  const gfloat* ia = as_global(S.fia);
+  const gfloat* fu = (const gfloat*)S.fu;
+  const gfloat* fv = (const gfloat*)S.fv;
+  float2* part = twl + p;                // [pd][cb]
+  for (int e = threadIdx.x; e < pd * cb; e += blockDim.x) {
+    const int i1 = e / cb, le = e - i1 * cb, bc = cblk * cbb + le % cbb;
+    if (bc >= qd) continue;
+    const int ce = bc + (le / cbb) * qd;
+    float tr = 0.f, ti = 0.f;            // sum over the column's entries of u c
+    for (int m1 = 0; m1 < d; ++m1) {
+      const int i = i1 + m1 * pd;
+      const float2 u = ldg2(fu + 2 * (unsigned)(i * q + ce)), c = sh[i * cb + le];
+      tr += u.x * c.x - u.y * c.y;
+      ti += u.x * c.y + u.y * c.x;
+    }
+    part[e] = make_float2(tr, ti);
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < pd * cb; e += blockDim.x) {
+    const int i1 = e / cb, le = e - i1 * cb, bl = le % cbb, bc = cblk * cbb + bl;
+    if (bc >= qd) continue;
+    const int ce = bc + (le / cbb) * qd;
+    float tr = 0.f, ti = 0.f;
+    for (int m2 = 0; m2 < d; ++m2) {
+      const float2 s2 = part[i1 * cb + m2 * cbb + bl];
+      tr += s2.x;
+      ti += s2.y;
+    }
+    for (int m1 = 0; m1 < d; ++m1) {
+      const int i = i1 + m1 * pd;
+      const float a = ia[(unsigned)(i * q + ce)];
+      const float2 v = ldg2(fv + 2 * (unsigned)(i * q + ce)), c = sh[i * cb + le];
+      sh[i * cb + le] =
+          make_float2(a * c.x - (v.x * tr - v.y * ti), a * c.y - (v.x * ti + v.y * tr));
     }
   }
   __syncthreads();
-  const int G = blockDim.x / tpl;
-  const int g = threadIdx.x / tpl;
-  const int tl = threadIdx.x - g * tpl;
-  if (!S.fused) {
-    // 1/den of the line's points is requested before the forward transform, so its latency
-    // overlaps the transform (a line has at most 8 tpl points)
-    const gfloat* invden = as_global(S.invden);
-    for (int base = 0; base < cb; base += G) {
-      const int l = base + g;
-      const bool act = (g < G) && (l < cb);
-      const int t = act ? tl : tpl;
-      float2* line = sh + (act ? l : 0) * p;
-      const int col = act ? column(l) : -1;
-      float sv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = tl + u * tpl;
-        sv[u] = (col >= 0 && i < p) ? invden[(size_t)i * q + col] : 0.f;
-      }
-      fft_line<false>(line, S.fp, t, tpl, twl);
-      if (col >= 0) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int i = tl + u * tpl;
-          if (i < p) line[i] = cscale(line[i], sv[u]);
-        }
-      }
-      __syncthreads();
-      fft_line<true>(line, S.fp, t, tpl, twl);
-    }
-  } else {
-    for (int base = 0; base < cb; base += G) {
-      const int l = base + g;
-      const bool act = (g < G) && (l < cb);
-      fft_line<false>(sh + (act ? l : 0) * p, S.fp, act ? tl : tpl, tpl, twl);
-    }
-    // group solves: (i1, base column) pairs, i1 fastest (tables are column-major)
-    const int pd = p / d;
-    const gfloat* ia = as_global(S.fia);
-    const gfloat* fu = (const gfloat*)S.fu;
-    const gfloat* fv = (const gfloat*)S.fv;
-    for (int e = threadIdx.x; e < pd * cbb; e += blockDim.x) {
-      const int bcl = e / pd, i1 = e - bcl * pd;
-      if (cblk * cbb + bcl >= qd) continue;
-      const int col0 = cblk * cbb + bcl;
-      float tr = 0.f, ti = 0.f;          // t = sum_k u_k c_k
-      for (int m2 = 0; m2 < d; ++m2) {
-        const size_t cbase = (size_t)(col0 + m2 * qd) * p;
-        const float2* ln = sh + (m2 * cbb + bcl) * p;
-        for (int m1 = 0; m1 < d; ++m1) {
-          const int i = i1 + m1 * pd;
-          const float2 u = ldg2(fu + 2 * (cbase + i)), c = ln[i];
-          tr += u.x * c.x - u.y * c.y;
-          ti += u.x * c.y + u.y * c.x;
-        }
-      }
-      for (int m2 = 0; m2 < d; ++m2) {
-        const size_t cbase = (size_t)(col0 + m2 * qd) * p;
-        float2* ln = sh + (m2 * cbb + bcl) * p;
-        for (int m1 = 0; m1 < d; ++m1) {
-          const int i = i1 + m1 * pd;
-          const float a = ia[cbase + i];
-          const float2 v = ldg2(fv + 2 * (cbase + i)), c = ln[i];
-          ln[i] = make_float2(a * c.x - (v.x * tr - v.y * ti), a * c.y - (v.x * ti + v.y * tr));
-        }
-      }
-    }
-    __syncthreads();
-    for (int base = 0; base < cb; base += G) {
-      const int l = base + g;
-      const bool act = (g < G) && (l < cb);
-      fft_line<true>(sh + (act ? l : 0) * p, S.fp, act ? tl : tpl, tpl, twl);
-    }
-  }
-  if (pairs) {
-    const int cb2 = cb >> 1;
-    for (int e = threadIdx.x; e < cb2 * p; e += blockDim.x) {
-      const int i = e / cb2, l = 2 * (e - i * cb2), col = cblk * cb + l;
-      const float2 u = sh[l * p + i], w = sh[(l + 1) * p + i];
-      if (col + 1 < q)
-        stg4(Fm + 2 * ((size_t)i * q + col), make_float4(u.x, u.y, w.x, w.y));
-      else if (col < q)
-        stg2(Fm + 2 * ((size_t)i * q + col), u);
-    }
-    return;
-  }
-  for (int e = threadIdx.x; e < cb * p; e += blockDim.x) {
-    const int i = e / cb, l = e - i * cb, col = column(l);
-    if (col >= 0) stg2(Fm + 2 * ((size_t)i * q + col), sh[l * p + i]);
-  }
+  cols_from_lds(S, t, tpl, twl, brd, bwr, gout, sync);
 }
 
 // Inverse DFT along rows, unpack bands (2m, 2m+1) into X.
+// ADD: plus a [L][p][q] slot.
+template <bool ADD>
 __global__ void fft_rows_inv(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
                              int f_s, int x_s, int add_s) {
   extern __shared__ float2 sh[];
@@ -369,72 +444,54 @@ __global__ void fft_rows_inv(const SceneDesc* __restrict__ sd, const int2* __res
   const int nrb = ceil_div(p, lpb);
   const int m = it.y / nrb, row0 = (it.y - m * nrb) * lpb;
   const size_t plane = (size_t)p * q;
+  const int g = threadIdx.x / tpl, r = row0 + g;
+  const bool act = g < lpb && r < p;
+  const int t = act ? threadIdx.x - g * tpl : tpl;
+  const bool two = 2 * m + 1 < L;
   const gfloat* Fm = gslot<const gfloat>(S, f_s) + 2 * (size_t)m * plane;   // complex
-  float2* twl = sh + lpb * q;
+  const unsigned ro = (unsigned)r * q;
+  gfloat* Xa = gslot<gfloat>(S, x_s) + (size_t)(2 * m) * plane;
+  gfloat* Xb = Xa + (two ? plane : 0);
+  const gfloat* Aa = gslot<const gfloat>(S, ADD ? add_s : f_s) + (ADD ? (size_t)(2 * m) * plane : 0);
+  const gfloat* Ab = Aa + (two ? plane : 0);
+  float2* buf = sh + (act ? g : 0) * row_pos(q);
+  float2* twl = sh + lpb * row_pos(q);
   stage_twiddles(twl, S.fq);
-  const int q2 = q >> 1;                // two complex points per 16-byte load
-  for (int e = threadIdx.x; e < lpb * q2; e += blockDim.x) {
-    const int l = e / q2, i2 = e - l * q2, r = row0 + l;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < p) v = ldg4(Fm + 2 * ((size_t)r * q + 2 * i2));
-    sh[l * q + 2 * i2] = make_float2(v.x, v.y);
-    sh[l * q + 2 * i2 + 1] = make_float2(v.z, v.w);
-  }
-  __syncthreads();
-  const int g = threadIdx.x / tpl;
-  const int t = (g < lpb) ? threadIdx.x - g * tpl : tpl;
-  fft_line<true>(sh + (g < lpb ? g : 0) * q, S.fq, t, tpl, twl);
-  gfloat* X = gslot<gfloat>(S, x_s);
-  gfloat* Xa = X + (size_t)(2 * m) * plane;
-  gfloat* Xb = (2 * m + 1 < L) ? X + (size_t)(2 * m + 1) * plane : nullptr;
-  const gfloat* Ad = add_s < 0 ? nullptr : gslot<const gfloat>(S, add_s);
-  const gfloat* Aa = Ad ? Ad + (size_t)(2 * m) * plane : nullptr;
-  const gfloat* Ab = (Ad && Xb) ? Ad + (size_t)(2 * m + 1) * plane : nullptr;
-  const uintptr_t align = reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Ad);
-  if ((align & 15) == 0) {              // 16-byte stores of 4 points of a row (q % 4 == 0)
-    const int q4 = q >> 2;
-    for (int e = threadIdx.x; e < lpb * q4; e += blockDim.x) {
-      const int l = e / q4, i4 = e - l * q4, r = row0 + l;
-      if (r >= p) continue;
-      const float2* s4 = sh + l * q + 4 * i4;
-      const float2 v0 = s4[0], v1 = s4[1], v2 = s4[2], v3 = s4[3];
-      const size_t o = (size_t)r * q + 4 * i4;
-      float4 a = make_float4(v0.x, v1.x, v2.x, v3.x);
-      if (Aa) {
-        const float4 t = ldg4(Aa + o);
-        a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
-      }
-      stg4(Xa + o, a);
-      if (Xb) {
-        float4 b = make_float4(v0.y, v1.y, v2.y, v3.y);
-        if (Ab) {
-          const float4 t = ldg4(Ab + o);
-          b.x += t.x; b.y += t.y; b.z += t.z; b.w += t.w;
-        }
-        stg4(Xb + o, b);
-      }
-    }
-    return;
-  }
-  for (int e = threadIdx.x; e < lpb * q; e += blockDim.x) {
-    const int l = e / q, i = e - l * q, r = row0 + l;
-    if (r < p) {
-      const float2 v = sh[e];
-      const size_t o = (size_t)r * q + i;
-      Xa[o] = Aa ? v.x + Aa[o] : v.x;
-      if (Xb) Xb[o] = Ab ? v.y + Ab[o] : v.y;
-    }
-  }
+  const bool in_wave = 64 % tpl == 0;
+  fft_line<true>(
+      S.fq, t, tpl, twl, [&](int, int, int i) { return ldg2(Fm + 2 * (ro + i)); },
+      [&](int, int, int i, float2 v) {
+        Xa[ro + i] = ADD ? v.x + Aa[ro + i] : v.x;
+        if (two) Xb[ro + i] = ADD ? v.y + Ab[ro + i] : v.y;
+      },
+      [&](int, int, int i) { return buf[row_pos(i)]; },
+      [&](int, int, int i, float2 v) { buf[row_pos(i)] = v; }, [] { __syncthreads(); },
+      [&] { line_sync(in_wave); });
 }
 
+// LDS of a row workgroup: the lines (padded) and a line of twiddles; of a column workgroup: the
+// lines, a line of twiddles and, for fused-S, the partial sums of the group solves
 constexpr size_t kFftLds = 65536;
+size_t rows_bytes(int q, int lpb) {
+  return ((size_t)lpb * (q + q / 8) + q) * sizeof(float2);
+}
+size_t cols_bytes(int p, int cb, int d_fused) {
+  return ((size_t)(cb + 1) * p + (d_fused > 0 ? (size_t)cb * (p / d_fused) : 0)) * sizeof(float2);
+}
+// a column group of fused-S is at least d columns: beyond 64 KiB by its partial sums at most
+size_t cols_max(int p, int d_fused) {
+  return std::max(kFftLds, d_fused > 0 ? cols_bytes(p, d_fused, d_fused) : 0);
+}
 
 int launch_rows(const Batch& B, bool inv, int a, int b, int add, hipStream_t s) {
   for (const Group& g : B.groups[KD_ROWS]) {
     if (!g.nitems) continue;
-    if (inv)
-      hipLaunchKernelGGL(fft_rows_inv, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
+    if (inv && add >= 0)
+      hipLaunchKernelGGL(fft_rows_inv<true>, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
                          g.d_items, a, b, add);
+    else if (inv)
+      hipLaunchKernelGGL(fft_rows_inv<false>, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
+                         g.d_items, a, b, -1);
     else
       hipLaunchKernelGGL(fft_rows_fwd, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
                          g.d_items, a, b);
@@ -461,8 +518,8 @@ int fft_block(int tpl) {
   return b;
 }
 
-// Workgroup size for `lines` lines of tpl threads each: at least fft_block(tpl), and up to
-// 1024 so that all lines of the block are transformed in one round.
+// Workgroup size for `lines` lines of tpl threads each (at most 1024 in all): at least
+// fft_block(tpl), and every line of the block has its threads.
 static int lines_block(int tpl, int lines) {
   int b = fft_block(tpl);
   while (b < lines * tpl && b < 1024) b *= 2;
@@ -475,9 +532,10 @@ int rows_blocks(const Plan& P) {
 int cols_blocks(const Plan& P) {
   return ceil_div(P.prm.q, P.fft.p_cb) * ((P.Lx + 1) / 2);
 }
-// data lines plus one line of twiddles
-size_t rows_lds(const Plan& P) { return (size_t)(P.fft.q_lpb + 1) * P.prm.q * sizeof(float2); }
-size_t cols_lds(const Plan& P) { return (size_t)(P.fft.p_cb + 1) * P.prm.p * sizeof(float2); }
+size_t rows_lds(const Plan& P) { return rows_bytes(P.prm.q, P.fft.q_lpb); }
+size_t cols_lds(const Plan& P) {
+  return cols_bytes(P.prm.p, P.fft.p_cb, P.d_fia ? P.prm.d : 0);
+}
 
 // d_fused > 0: the columns per block must be a multiple of d (a base column and its aliases)
 FftShape default_fft_shape(int p, int q, int d_fused) {
@@ -485,15 +543,33 @@ FftShape default_fft_shape(int p, int q, int d_fused) {
   f.q_tpl = ceil_div(q, 8);
   f.p_tpl = ceil_div(p, 8);
   f.q_lpb = fft_block(f.q_tpl) / f.q_tpl;
-  while (f.q_lpb > 1 && (size_t)(f.q_lpb + 1) * q * sizeof(float2) > kFftLds) --f.q_lpb;
+  while (f.q_lpb > 1 && rows_bytes(q, f.q_lpb) > kFftLds) --f.q_lpb;
   const int unit = d_fused > 0 ? d_fused : 1;
   f.p_cb = unit;
-  while (f.p_cb * 2 <= std::max(16, unit) &&
-         (size_t)(f.p_cb * 2 + 1) * p * sizeof(float2) <= kFftLds)
+  while (f.p_cb * 2 <= std::max(16, unit) && f.p_cb * 2 * f.p_tpl <= 1024 &&
+         cols_bytes(p, f.p_cb * 2, d_fused) <= kFftLds)
     f.p_cb *= 2;
   f.q_bs = fft_block(f.q_tpl);
-  f.p_bs = fft_block(f.p_tpl);
+  f.p_bs = lines_block(f.p_tpl, f.p_cb);
   return f;
+}
+
+// A launch over scenes of several sizes has one workgroup size; threads without a line of their
+// scene would only wait.  So a scene of a batch takes as many lines as fill workgroups of about
+// the same size: 256 threads for the rows, 512 for the columns (more where one line, or one
+// column group of fused-S, needs it).
+void batch_fft_shape(Plan& P) {
+  const int p = P.prm.p, q = P.prm.q, dfu = P.d_fia ? P.prm.d : 0;
+  FftShape f = default_fft_shape(p, q, dfu);
+  f.q_bs = fft_block(f.q_tpl);
+  f.q_lpb = f.q_bs / f.q_tpl;
+  const int unit = dfu > 0 ? dfu : 1;
+  f.p_cb = unit;
+  while (f.p_cb * 2 <= std::max(32, unit) && f.p_cb * 2 * f.p_tpl <= 512 &&
+         cols_bytes(p, f.p_cb * 2, dfu) <= kFftLds)
+    f.p_cb *= 2;
+  f.p_bs = lines_block(f.p_tpl, f.p_cb);
+  P.fft = f;
 }
 
 int launch_xsolve(const Batch& B, int c, int x, int f, int add, hipStream_t s) {
@@ -550,6 +626,14 @@ int autotune_fft(Plan& P) {
     set_error("autotune: allocation failed");
     return NLPR_ERR_HIP;
   }
+  if (cols_max(p, dfu) > kFftLds &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(fft_cols_solve),
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)kMaxSweepLds) != hipSuccess) {
+    cleanup();
+    set_error("autotune: the column pass needs more LDS than a workgroup can have");
+    return NLPR_ERR_HIP;
+  }
   hipMemset(d_real, 0, 2 * tp * plane * sizeof(float));
   std::vector<int2> items(maxitems);
   for (int i = 0; i < maxitems; ++i) items[i] = make_int2(0, i);
@@ -589,17 +673,17 @@ int autotune_fft(Plan& P) {
     const int tpl = best.q_tpl;
     float tbest = 1e30f;
     for (int lpb = 1; lpb * tpl <= 1024; lpb *= 2) {
-      if ((size_t)(lpb + 1) * q * sizeof(float2) > kFftLds) break;
+      if (rows_bytes(q, lpb) > kFftLds) break;
       const int bs = lines_block(tpl, lpb);
       h.fq_tpl = tpl;
       h.fq_lpb = lpb;
       hipMemcpy(d_sd, &h, sizeof(SceneDesc), hipMemcpyHostToDevice);
       const int nb = ceil_div(p, lpb) * tp;
-      const size_t lds = (size_t)(lpb + 1) * q * sizeof(float2);
+      const size_t lds = rows_bytes(q, lpb);
       const float ms = time_it([&]() {
         hipLaunchKernelGGL(fft_rows_fwd, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items, (int)B_C,
                            (int)B_F);
-        hipLaunchKernelGGL(fft_rows_inv, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items, (int)B_F,
+        hipLaunchKernelGGL(fft_rows_inv<false>, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items, (int)B_F,
                            (int)B_Z, -1);
       });
       if (hipGetLastError() != hipSuccess) { rc = NLPR_ERR_HIP; break; }
@@ -610,14 +694,14 @@ int autotune_fft(Plan& P) {
   if (rc == NLPR_OK) {
     const int tpl = best.p_tpl;
     float tbest = 1e30f;
-    for (int cb = std::max(dfu, 1); cb <= std::max(32, dfu); cb *= 2) {
-      if ((size_t)(cb + 1) * p * sizeof(float2) > kFftLds) break;
+    for (int cb = std::max(dfu, 1); cb <= std::max(32, dfu) && cb * tpl <= 1024; cb *= 2) {
+      if (cols_bytes(p, cb, dfu) > cols_max(p, dfu)) break;
       const int bs = lines_block(tpl, cb);
       h.fp_tpl = tpl;
       h.fp_cb = cb;
       hipMemcpy(d_sd, &h, sizeof(SceneDesc), hipMemcpyHostToDevice);
       const int nb = ceil_div(q, cb) * tp;
-      const size_t lds = (size_t)(cb + 1) * p * sizeof(float2);
+      const size_t lds = cols_bytes(p, cb, dfu);
       const float ms = time_it([&]() {
         hipLaunchKernelGGL(fft_cols_solve, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items,
                            (int)B_F);

@@ -88,7 +88,7 @@ struct SceneDesc {
   const float* E;                  // [Ls][Lz]
   const float* Ep;                 // E^+ = E^T (E E^T)^{-1}, [Lz][Ls]
   const float* M;                  // (E E^T + rho I)^{-1}, [Ls][Ls]
-  // fused-S X-update tables, column-major [q][p]: 1/(a p q), b^/a, gamma conj(b^)/(a p q)
+  // fused-S X-update tables, [p][q]: 1/(a p q), b^/a, gamma conj(b^)/(a p q)
   const float* fia;
   const float2* fu;
   const float2* fv;
@@ -393,5 +393,6 @@ size_t sweep_sigma_bytes(const SweepShape& sh, int q, int L, int npairs, int npa
 int fft_block(int tpl);             // workgroup size of a line FFT with tpl threads per line
 int autotune_fft(Plan& P);          // picks P.fft by timing candidates (cached per (p, q, d if fused))
 FftShape default_fft_shape(int p, int q, int d_fused);
+void batch_fft_shape(Plan& P);      // P.fft of a scene of a batch
 
 }  // namespace nlpr

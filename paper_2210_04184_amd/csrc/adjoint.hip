@@ -431,15 +431,18 @@ mubar_reduce_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ i
 // where G' = sum res s^T and dG/drho = -G G / lambda1 give -res^T G (G s) / lambda1 per
 // pixel.  The band sums res = Y_h - A0 R and s = P2' R are formed per share and added in
 // LDS in a fixed order.
+// BX' overwrites W1', from which it differs on the sampled pixels only, and Lambda2'' is -X'
+// (xp_s, read before it is rewritten): 20 bytes per pixel and band instead of 36, 28.2 -> 24.2 us
+// at 256 x 256 x 31.
 // Bands [c0, c1) of one pixel in the P-update adjoint: X', Lambda2'', BX', Lambda1'' and
 // Y_l' of the step; returns the pixel's rho' share through P1.  Restrict parameters let the
 // compiler read R with scalar loads across the stores.
 template <int LHM>
 __device__ __forceinline__ double pupdate_bwd_write(
     const gfloat* __restrict__ BX, const gfloat* __restrict__ Yl, const gfloat* __restrict__ L1,
-    const gfloat* __restrict__ W1b, const gfloat* __restrict__ W2b, gfloat* __restrict__ L1b,
-    gfloat* __restrict__ L2b, gfloat* __restrict__ BXb, gfloat* __restrict__ Xp,
-    gfloat* __restrict__ GYl, const gfloat* __restrict__ R, const float (&v)[LHM], size_t plane,
+    gfloat* __restrict__ W1b, const gfloat* __restrict__ W2b, gfloat* __restrict__ L1b,
+    gfloat* __restrict__ Xp, gfloat* __restrict__ GYl, const gfloat* __restrict__ R,
+    const float (&v)[LHM], size_t plane,
     size_t lplane, size_t lj, bool sampled, int Lh, float inv, float rr, int c0, int c1, int j) {
   double acc = 0.0;
   for (int c = c0; c < c1; ++c) {
@@ -450,23 +453,18 @@ __device__ __forceinline__ double pupdate_bwd_write(
       if (h < Lh) corr += v[h] * R[c * Lh + h];
     // with P2' = 2 W2' + Lambda2'' and A0' = P2' - P2' R G R^T = P2' - corr:
     // X' = A0' - W2' - Lambda2'' = W2' - corr and Lambda2''(new) = W2' + Lambda2'' - A0'
-    // = corr - W2', so Lambda2'' is not read again here
-    const float xp = W2b[o] - corr;
-    Xp[o] = xp;
-    L2b[o] = -xp;
-    const float w1b = W1b[o];
+    // = corr - W2' = -X', so it needs no plane of its own.  Off the sampled pixels BX' = W1' and
+    // Lambda1'' is not read again, so W1' stays as it is
+    Xp[o] = W2b[o] - corr;
     if (sampled) {
-      const float l1b = L1b[o];            // read only where the P1 step keeps it
+      const float w1b = W1b[o], l1b = L1b[o];
       const float p1b = 2.f * w1b + l1b;
       const float y = Yl[c * lplane + lj];
-      BXb[o] = -w1b - l1b + p1b * rr;
+      W1b[o] = -w1b - l1b + p1b * rr;
       L1b[o] = w1b + l1b - p1b * rr;
       GYl[c * lplane + lj] += p1b * inv;
       acc += (double)p1b * ((double)BX[o] - (double)L1[o] - (double)y) * (double)inv *
              (double)inv;
-    } else {
-      BXb[o] = w1b;
-      L1b[o] = -w1b;
     }
   }
   return acc;
@@ -476,9 +474,9 @@ __device__ __forceinline__ double pupdate_bwd_write(
 template <int LHM, int KB>
 __device__ __forceinline__ double pupdate_bwd_write_kept(
     const gfloat* __restrict__ BX, const gfloat* __restrict__ Yl, const gfloat* __restrict__ L1,
-    const gfloat* __restrict__ W1b, const float (&w2k)[KB], gfloat* __restrict__ L1b,
-    gfloat* __restrict__ L2b, gfloat* __restrict__ BXb, gfloat* __restrict__ Xp,
-    gfloat* __restrict__ GYl, const gfloat* __restrict__ R, const float (&v)[LHM], size_t plane,
+    gfloat* __restrict__ W1b, const float (&w2k)[KB], gfloat* __restrict__ L1b,
+    gfloat* __restrict__ Xp, gfloat* __restrict__ GYl, const gfloat* __restrict__ R,
+    const float (&v)[LHM], size_t plane,
     size_t lplane, size_t lj, bool sampled, int Lh, float inv, float rr, int c0, int c1, int j) {
   float w1a[KB], l1ba[KB], yla[KB], bxa[KB], l1a[KB], gya[KB];
 #pragma unroll
@@ -486,8 +484,8 @@ __device__ __forceinline__ double pupdate_bwd_write_kept(
     if (c0 + i < c1) {
       const int c = c0 + i;
       const size_t o = (size_t)c * plane + j;
-      w1a[i] = W1b[o];
       if (sampled) {
+        w1a[i] = W1b[o];
         l1ba[i] = L1b[o];
         yla[i] = Yl[c * lplane + lj];
         bxa[i] = BX[o];
@@ -505,22 +503,16 @@ __device__ __forceinline__ double pupdate_bwd_write_kept(
 #pragma unroll
       for (int h = 0; h < LHM; ++h)
         if (h < Lh) corr += v[h] * R[c * Lh + h];
-      const float xp = w2k[i] - corr;
-      Xp[o] = xp;
-      L2b[o] = -xp;
-      const float w1b = w1a[i];
+      Xp[o] = w2k[i] - corr;
       if (sampled) {
-        const float l1b = l1ba[i];
+        const float w1b = w1a[i], l1b = l1ba[i];
         const float p1b = 2.f * w1b + l1b;
         const float y = yla[i];
-        BXb[o] = -w1b - l1b + p1b * rr;
+        W1b[o] = -w1b - l1b + p1b * rr;
         L1b[o] = w1b + l1b - p1b * rr;
         GYl[c * lplane + lj] = gya[i] + p1b * inv;
         acc += (double)p1b * ((double)bxa[i] - (double)l1a[i] - (double)y) * (double)inv *
                (double)inv;
-      } else {
-        BXb[o] = w1b;
-        L1b[o] = -w1b;
       }
     }
   return acc;
@@ -534,7 +526,7 @@ template <int LHM, int PB_NC, bool KEEP>
 __global__ void __launch_bounds__(256 * PB_NC)
 pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                    int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1b_s, int w2b_s,
-                   int l1b_s, int l2b_s, int bxb_s, int xp_s, int gyl_s, int gyh_s, int part_s) {
+                   int l1b_s, int xp_s, int gyl_s, int gyh_s, int part_s) {
   __shared__ float part[PB_NC > 1 ? PB_NC : 1][PB_NC > 1 ? LHM : 1][PB_NC > 1 ? 256 : 1];
   const int2 it = items[blockIdx.x];
   const SceneDesc& S = sd[it.x];
@@ -550,7 +542,7 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
   const gfloat* X = gslot<const gfloat>(S, x_s);
   const gfloat* L2 = gslot<const gfloat>(S, l2_s);
   const gfloat* W2b = gslot<const gfloat>(S, w2b_s);
-  gfloat* L2b = gslot<gfloat>(S, l2b_s);
+  const gfloat* Xo = gslot<const gfloat>(S, xp_s);   // X' of the step before = -Lambda2''
   const gfloat* R = as_global(S.R);
   const gfloat* G = as_global(S.G);
   float rp[LHM], sp[LHM];
@@ -559,7 +551,7 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
   constexpr int KB = KEEP ? kPbKeep : 1;
   float w2k[KB];                        // W2' of the thread's bands (KEEP)
   if (KEEP && act) {
-    float xa[KB], l2a[KB], l2ba[KB];
+    float xa[KB], l2a[KB], xoa[KB];
 #pragma unroll
     for (int i = 0; i < KB; ++i)
       if (c0 + i < c1) {
@@ -567,14 +559,14 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
         xa[i] = X[o];
         l2a[i] = L2[o];
         w2k[i] = W2b[o];
-        l2ba[i] = L2b[o];
+        xoa[i] = Xo[o];
       }
 #pragma unroll
     for (int i = 0; i < KB; ++i)
       if (c0 + i < c1) {
         const int c = c0 + i;
         const float a0 = xa[i] - l2a[i];
-        const float p2b = 2.f * w2k[i] + l2ba[i];
+        const float p2b = 2.f * w2k[i] - xoa[i];
 #pragma unroll
         for (int h = 0; h < LHM; ++h)
           if (h < Lh) {
@@ -587,7 +579,7 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
     for (int c = c0; c < c1; ++c) {      // this quarter's A0 R and P2' R
       const size_t o = (size_t)c * plane + j;
       const float a0 = X[o] - L2[o];
-      const float p2b = 2.f * W2b[o] + L2b[o];
+      const float p2b = 2.f * W2b[o] - Xo[o];
 #pragma unroll
       for (int h = 0; h < LHM; ++h)
         if (h < Lh) {
@@ -631,9 +623,8 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
     const gfloat* Yl = gslot<const gfloat>(S, yl_s);
     const gfloat* Yh = gslot<const gfloat>(S, yh_s);
     const gfloat* L1 = gslot<const gfloat>(S, l1_s);
-    const gfloat* W1b = gslot<const gfloat>(S, w1b_s);
+    gfloat* W1b = gslot<gfloat>(S, w1b_s);
     gfloat* L1b = gslot<gfloat>(S, l1b_s);
-    gfloat* BXb = gslot<gfloat>(S, bxb_s);
     gfloat* Xp = gslot<gfloat>(S, xp_s);
     gfloat* GYl = gslot<gfloat>(S, gyl_s);
     gfloat* GYh = gslot<gfloat>(S, gyh_s);
@@ -669,11 +660,11 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
         if (h < Lh) GYh[h * plane + j] += v[h];
     }
     if constexpr (KEEP)
-      acc[0] = pupdate_bwd_write_kept<LHM, KB>(BX, Yl, L1, W1b, w2k, L1b, L2b, BXb, Xp, GYl, R,
+      acc[0] = pupdate_bwd_write_kept<LHM, KB>(BX, Yl, L1, W1b, w2k, L1b, Xp, GYl, R,
                                                v, plane, lplane, lj, sampled, Lh, inv, rr, c0,
                                                c1, j);
     else
-      acc[0] = pupdate_bwd_write<LHM>(BX, Yl, L1, W1b, W2b, L1b, L2b, BXb, Xp, GYl, R, v, plane,
+      acc[0] = pupdate_bwd_write<LHM>(BX, Yl, L1, W1b, W2b, L1b, Xp, GYl, R, v, plane,
                                       lplane, lj, sampled, Lh, inv, rr, c0, c1, j);
   }
   block_sum_waves<2, 4 * PB_NC>(acc);
@@ -956,27 +947,25 @@ int launch_mubar_reduce(const Batch& B, int mup, int mub, hipStream_t s) {
 
 template <int LHM, int NC>
 void launch_pb(const Batch& B, const Group& g, int x, int bx, int yl, int yh, int l1, int l2,
-               int w1b, int w2b, int l1b, int l2b, int bxb, int xp, int gyl, int gyh, int part,
-               hipStream_t s) {
+               int w1b, int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s) {
   // the reverse mode takes one scene: its bands per thread decide the variant
   if (ceil_div(B.scenes[0]->Lx, NC) <= kPbKeep)
     hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, true>), dim3(g.nitems), dim3(256 * NC), 0,
-                       s, B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, l2b, bxb,
-                       xp, gyl, gyh, part);
+                       s, B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
+                       gyl, gyh, part);
   else
     hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, false>), dim3(g.nitems), dim3(256 * NC), 0,
-                       s, B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, l2b, bxb,
-                       xp, gyl, gyh, part);
+                       s, B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
+                       gyl, gyh, part);
 }
 
 int launch_pupdate_bwd(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1b,
-                       int w2b, int l1b, int l2b, int bxb, int xp, int gyl, int gyh, int part,
-                       hipStream_t s) {
+                       int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s) {
   for (const Group& g : B.groups[KD_PIXEL]) {
     if (!g.nitems) continue;
     const bool split = g.key1 == 4;
 #define NLPR_PB(LHM, NC) \
-  launch_pb<LHM, NC>(B, g, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, l2b, bxb, xp, gyl, gyh, part, s)
+  launch_pb<LHM, NC>(B, g, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp, gyl, gyh, part, s)
     if (g.key0 == 1) {
       if (split) NLPR_PB(1, 4); else NLPR_PB(1, 1);
     } else if (g.key0 == 4) {

@@ -704,15 +704,18 @@ int enqueue_solve(Batch& B, bool resume, hipStream_t s) {
       NLPR_HIP_TRY(hipStreamWaitEvent(B.side, B.fork_ev, 0));
       sp = B.side;
     }
-    if (!fused || mon) {           // fused-S needs B X only for the monitor's data term
+    // B X goes straight into W1, where the P-update changes the sampled pixels only; a monitor
+    // record reads B X beside W1.  (fused-S needs B X only for the monitor's data term.)
+    const int bx = fused || mon ? B_BX : B_W1;
+    if (!fused || mon) {
       StageTimer tm(B, sp, NLPR_STAGE_BLUR);
-      if ((rc = launch_conv(B, B_Z, B_BX, false, -1, -1, -1, 0, sp))) return rc;
+      if ((rc = launch_conv(B, B_Z, bx, false, -1, -1, -1, 0, sp))) return rc;
     }
     {
       StageTimer tm(B, sp, NLPR_STAGE_PUPDATE);
-      if ((rc = launch_pupdate(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, sp)))
+      if ((rc = launch_pupdate(B, B_Z, bx, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, -1, sp)))
         return rc;
-      if (sub && (rc = launch_p1_subspace(B, B_BX, B_YLE, B_L1, B_W1, sp))) return rc;
+      if (sub && (rc = launch_p1_subspace(B, bx, B_YLE, B_L1, B_W1, sp))) return rc;
     }
     if (tpart && (rc = launch_conv(B, B_W1, B_BX, true, B_W2, -1, -1, 0, sp))) return rc;
     if (mon) {
@@ -842,7 +845,8 @@ int batch_solve(Batch& B, const float* const* Yl, const float* const* Yh, float*
 
 // ---------------------------------------------------------------------- reverse mode
 // Checkpoints, for t = 1 .. T-1: X^t, B X^t and the Lambda1, Lambda2 entering iteration t
-// (planes), then the threshold branches of iteration t's sweep (2 bits per dual element).
+// (planes; B X and Lambda1 on the sampled pixels, the only ones the reverse step reads), then
+// the threshold branches of iteration t's sweep (2 bits per dual element).
 // Layout: the 4 (T - 1) planes first ([t][X, BX, Lambda1, Lambda2]), then the T - 1 blocks
 // of branch codes.
 struct GradLayout {
@@ -860,7 +864,7 @@ GradLayout grad_layout(const Plan& P) {
     G.off[slot] = off;
     off = align256(off + std::max<size_t>(bytes, 4));
   };
-  for (int k : {B_GC, B_GCP, B_GL1, B_GL2, B_GX, B_GW1, B_GBX, B_GXP, B_GXR}) take(k, pl);
+  for (int k : {B_GC, B_GCP, B_GL1, B_GX, B_GW1, B_GXP, B_GXR}) take(k, pl);
   const size_t mup = (size_t)P.npairs * P.prm.p * P.prm.q * sizeof(float);
   G.npix = pixel_blocks(P);
   G.nw = P.npairs ? weights_bwd_blocks(P) : 0;
@@ -907,7 +911,7 @@ uint8_t* ck_codes(void* ck, const GradLayout& G, int T, int t) {
 // Forward solve that keeps the checkpoints.  Z = X^T equals nlpr_solve's output bit for bit;
 // the last iteration stops after its X-update, the only part of it that reaches Z.  Nothing
 // is copied: before each iteration the descriptor's slots are re-pointed so that the X-update
-// and the blur write X^t and B X^t into checkpoint t, and the P-update reads the Lambda of
+// writes X^t into checkpoint t, and the P-update writes B X^t there, reads the Lambda of
 // checkpoint t and writes the new Lambda into checkpoint t+1 (the workspace after the last).
 // The sweep updates Sigma' in place in the workspace, as in the solve, and writes the branch
 // codes of checkpoint t.
@@ -936,6 +940,9 @@ int grad_forward(Batch& B, const float* Yl, const float* Yh, float* Z, void* ws,
   void* wl1 = base + P.off[B_L1];
   void* wl2 = base + P.off[B_L2];
   if ((rc = launch_weights(B, B_YH, B_MU, s))) return rc;
+  // Lambda1 is zero off the sampled pixels, which alone the checkpoints carry: the workspace's
+  // plane, which takes it after the last P-update, gets its zeros here
+  if ((rc = launch_fill(B, B_L1, s))) return rc;
   if (T > 1) {                   // the start's Lambda (zeros) goes into checkpoint 1
     SlotSet st;
     st.add(B_L1, plane(1, 2));
@@ -960,8 +967,8 @@ int grad_forward(Batch& B, const float* Yl, const float* Yh, float* Z, void* ws,
     }
     if ((rc = launch_xsolve(B, B_C, B_Z, B_F, -1, s))) return rc;
     if (t == T) break;
-    if ((rc = launch_conv(B, B_Z, B_BX, false, -1, -1, -1, 0, s))) return rc;
-    if ((rc = launch_pupdate(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1O, B_L2O, s)))
+    if ((rc = launch_conv(B, B_Z, B_W1, false, -1, -1, -1, 0, s))) return rc;
+    if ((rc = launch_pupdate(B, B_Z, B_W1, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1O, B_L2O, B_BX, s)))
       return rc;
     if (reg && (rc = launch_sweep(B, B_Z, B_MU, B_SIGMA, B_C, B_HALO, t == 1, s,
                                   ck_codes(ck, G, T, t))))
@@ -994,8 +1001,8 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
   char* gb = static_cast<char*>(gws);
   // X, B X and Lambda of each iteration are read from its checkpoint (slots re-pointed)
   SceneDesc d = solve_desc(P, base, Yl, Yh, reinterpret_cast<float*>(base + P.off[B_W2]));
-  for (int k : {B_GC, B_GCP, B_GL1, B_GL2, B_GX, B_GW1, B_GBX, B_GXP, B_GXR, B_GSIG, B_GHALO,
-                B_GMUP, B_GMU, B_GE, B_GPART})
+  for (int k : {B_GC, B_GCP, B_GL1, B_GX, B_GW1, B_GXP, B_GXR, B_GSIG, B_GHALO, B_GMUP, B_GMU,
+                B_GE, B_GPART})
     d.buf[k] = gb + G.off[k];
   // C' alternates between two buffers, so that the sweep adjoint of step t still has the C'
   // of step t + 1 (slot B_GCP), from which it rebuilds the Sigma'' that step did not store
@@ -1014,7 +1021,7 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
   const int p = P.prm.p, q = P.prm.q, d_ = P.prm.d;
   const size_t pl = (size_t)P.Lx * p * q * sizeof(float);
   NLPR_HIP_TRY(hipMemsetAsync(gb + G.off[B_GL1], 0, pl, s));
-  NLPR_HIP_TRY(hipMemsetAsync(gb + G.off[B_GL2], 0, pl, s));
+  NLPR_HIP_TRY(hipMemsetAsync(gb + G.off[B_GXP], 0, pl, s));   // -Lambda2'' of the last iteration
   if (reg)
     NLPR_HIP_TRY(hipMemsetAsync(gb + G.off[B_GMUP], 0, mubar_partial_elems(P) * sizeof(float), s));
   NLPR_HIP_TRY(hipMemsetAsync(gb + G.off[B_GPART], 0, 2 * (size_t)(G.npix + G.nw) * sizeof(double), s));
@@ -1035,11 +1042,11 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
                                       B_GMUP, t + 1 < T ? ck_codes(ck, G, T, t + 1) : nullptr,
                                       B_GCP, s)))
       return rc;
-    if ((rc = launch_pupdate_bwd(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_GW1, B_GC, B_GL1, B_GL2,
-                                 B_GBX, B_GXP, B_GYL, B_GYH, B_GPART, s)))
+    if ((rc = launch_pupdate_bwd(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_GW1, B_GC, B_GL1, B_GXP,
+                                 B_GYL, B_GYH, B_GPART, s)))
       return rc;
     // X' = B^T BX' + X'(P-update) + X'(sweep) (+ halo rows)
-    if ((rc = launch_conv(B, B_GBX, B_GX, true, B_GXP, B_GXR, B_GHALO, 2, s))) return rc;
+    if ((rc = launch_conv(B, B_GW1, B_GX, true, B_GXP, B_GXR, B_GHALO, 2, s))) return rc;
     if ((rc = launch_xsolve(B, B_GX, B_GCP, B_F, -1, s))) return rc;   // C' of step t - 1
   }
   if (T > 1) {                   // C' of the start was written into buffer 0
@@ -1420,7 +1427,7 @@ int nlpr_debug_stage(nlpr_plan* plan, int stage, void* const* bufs, int32_t nbuf
       put(B_Z, 0); put(B_BX, 1); put(B_YL, 2); put(B_YH, 3); put(B_L1, 4); put(B_L2, 5);
       put(B_W1, 6); put(B_W2, 7);
       return run([&] {
-        return launch_pupdate(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, s);
+        return launch_pupdate(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, -1, s);
       });
     case NLPR_STAGE_SWEEP:
     case NLPR_STAGE_SWEEP_FIRST:

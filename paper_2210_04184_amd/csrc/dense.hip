@@ -292,10 +292,10 @@ p1_subspace_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
   const int Ls = S.L;
   const size_t plane = (size_t)S.p * S.q;
   const size_t j = (size_t)(m / qd) * S.d * S.q + (size_t)(m % qd) * S.d;
-  const gfloat* __restrict__ BX = gslot<const gfloat>(S, bx_s);
+  const gfloat* BX = gslot<const gfloat>(S, bx_s);    // may be W1
   const gfloat* __restrict__ yle = gslot<const gfloat>(S, yle_s);
   gfloat* __restrict__ L1 = gslot<gfloat>(S, l1_s);
-  gfloat* __restrict__ W1 = gslot<gfloat>(S, w1_s);
+  gfloat* W1 = gslot<gfloat>(S, w1_s);
   const gfloat* __restrict__ M = as_global(S.M);
   const float rho = S.rho;
   float v[kMaxLs], bx[kMaxLs], l1[kMaxLs];
@@ -732,6 +732,12 @@ conv_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, in
 // bands is summed per band share and the parts are added in share order (through LDS when a
 // pixel has several threads).
 //   Lambda1 -= BX - P1,  Lambda2 -= X - P2;  W1 = P1 + Lambda1,  W2 = P2 + Lambda2
+// Off the sampled pixels P1 = BX - Lambda1 gives Lambda1 = Lambda1 - (BX - P1) = 0 and W1 = BX,
+// exactly, from Lambda1 = 0 at the start: so when B X arrives in W1 (bx_s == w1_s) only the
+// sampled pixels, one in d^2, have a P1 to update.  Per pixel and band that leaves 16 bytes (X
+// and Lambda2 read, Lambda2 and W2 written) of 32: a 12-scene batch, whose P-update runs beside
+// the sweep, 16.6 -> 15.7 ms per 10-iteration solve; 256 x 256 x 31, where the launch is bound by
+// latency, 15.1 -> 14.7 us.
 // Band shares of the contraction A0 R in the P-update: fixed, so that the sum is the same
 // whichever number of threads a pixel has.
 constexpr int kPuShares = 4;
@@ -750,18 +756,18 @@ __device__ __forceinline__ void pupdate_share(const gfloat* __restrict__ X,
   }
 }
 
-// Bands [c0, c1) of one pixel: P2, Lambda2, W2 and (per p1mode) P1, Lambda1, W1.  Lambda is
-// read through L1, L2 and written through L1o, L2o, which may be the same buffers (no
-// restrict on those four).  R arrives as a restrict parameter so that the compiler may read
+// Bands [c0, c1) of one pixel: P2, Lambda2, W2 and, where p1, P1, Lambda1 and W1.  Lambda is
+// read through L1, L2 and written through L1o, L2o, which may be the same buffers, and BX may
+// be W1 (no restrict on those six); BXo, if not null, also takes B X where p1.  R arrives as a restrict parameter so that the compiler may read
 // it with scalar loads across the stores (restrict on local pointer variables is not used
 // for that).
 template <int LHM>
 __device__ __forceinline__ void pupdate_write(
-    const gfloat* __restrict__ X, const gfloat* __restrict__ BX, const gfloat* __restrict__ Yl,
-    const gfloat* L1, const gfloat* L2, gfloat* L1o, gfloat* L2o, gfloat* __restrict__ W1,
-    gfloat* __restrict__ W2, const gfloat* __restrict__ R, const float (&u)[LHM], size_t plane,
-    size_t lplane, size_t lj, bool sampled, int p1mode, int Lh, float rho, float inv_1prho,
-    int c0, int c1, int j) {
+    const gfloat* __restrict__ X, const gfloat* BX, const gfloat* __restrict__ Yl,
+    const gfloat* L1, const gfloat* L2, gfloat* L1o, gfloat* L2o, gfloat* W1,
+    gfloat* __restrict__ W2, gfloat* BXo, const gfloat* __restrict__ R, const float (&u)[LHM],
+    size_t plane, size_t lplane, size_t lj, bool sampled, bool p1, int Lh, float rho,
+    float inv_1prho, int c0, int c1, int j) {
   for (int c = c0; c < c1; ++c) {
     const size_t o = c * plane + j;
     float corr = 0.f;
@@ -773,12 +779,13 @@ __device__ __forceinline__ void pupdate_write(
     const float l2n = l2 - (x - p2);
     L2o[o] = l2n;
     W2[o] = p2 + l2n;
-    if (p1mode == 2 || (sampled && p1mode == 1)) continue;
+    if (!p1) continue;
     const float bx = BX[o], l1 = L1[o];
-    const float p1 = sampled ? (rho * bx + Yl[c * lplane + lj] - rho * l1) * inv_1prho : bx - l1;
-    const float l1n = l1 - (bx - p1);
+    const float p1v = sampled ? (rho * bx + Yl[c * lplane + lj] - rho * l1) * inv_1prho : bx - l1;
+    const float l1n = l1 - (bx - p1v);
     L1o[o] = l1n;
-    W1[o] = p1 + l1n;
+    W1[o] = p1v + l1n;
+    if (BXo) BXo[o] = bx;
   }
 }
 
@@ -792,8 +799,7 @@ constexpr int kPuKeep = 16;
 template <int LHM>
 __device__ __forceinline__ void pupdate_load_keep(const gfloat* __restrict__ X,
                                                   const gfloat* __restrict__ L2,
-                                                  const gfloat* __restrict__ BX,
-                                                  const gfloat* __restrict__ L1,
+                                                  const gfloat* BX, const gfloat* L1,
                                                   const gfloat* __restrict__ Yl, bool p1,
                                                   bool sampled, size_t plane, size_t lplane,
                                                   size_t lj, int c0, int c1, int j,
@@ -844,8 +850,8 @@ template <int LHM>
 __device__ __forceinline__ void pupdate_write_kept(
     const float (&xs)[kPuKeep], const float (&l2s)[kPuKeep], const float (&bxs)[kPuKeep],
     const float (&l1s)[kPuKeep], const float (&yls)[kPuKeep], gfloat* L1o, gfloat* L2o,
-    gfloat* __restrict__ W1, gfloat* __restrict__ W2, const gfloat* __restrict__ R,
-    const float (&u)[LHM], size_t plane, bool sampled, int p1mode, int Lh, float rho,
+    gfloat* __restrict__ W1, gfloat* __restrict__ W2, gfloat* BXo, const gfloat* __restrict__ R,
+    const float (&u)[LHM], size_t plane, bool sampled, bool p1, int Lh, float rho,
     float inv_1prho, int c0, int c1, int j) {
 #pragma unroll
   for (int i = 0; i < kPuKeep; ++i) {
@@ -861,12 +867,13 @@ __device__ __forceinline__ void pupdate_write_kept(
     const float l2n = l2 - (x - p2);
     L2o[o] = l2n;
     W2[o] = p2 + l2n;
-    if (p1mode == 2 || (sampled && p1mode == 1)) continue;
+    if (!p1) continue;
     const float bx = bxs[i], l1 = l1s[i];
-    const float p1 = sampled ? (rho * bx + yls[i] - rho * l1) * inv_1prho : bx - l1;
-    const float l1n = l1 - (bx - p1);
+    const float p1v = sampled ? (rho * bx + yls[i] - rho * l1) * inv_1prho : bx - l1;
+    const float l1n = l1 - (bx - p1v);
     L1o[o] = l1n;
-    W1[o] = p1 + l1n;
+    W1[o] = p1v + l1n;
+    if (BXo) BXo[o] = bx;
   }
 }
 
@@ -874,7 +881,7 @@ template <int LHM, int PU_NC, bool KEEP>
 __global__ void __launch_bounds__(256 * PU_NC)
 pupdate_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1_s, int w2_s, int l1o_s,
-               int l2o_s) {
+               int l2o_s, int bxo_s) {
   __shared__ float part[PU_NC > 1 ? PU_NC : 1][PU_NC > 1 ? LHM : 1][PU_NC > 1 ? 256 : 1];
   const int2 it = items[blockIdx.x];
   const SceneDesc& S = sd[it.x];
@@ -899,10 +906,9 @@ pupdate_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
   // KEEP: every scene of the launch has at most kPuKeep bands per thread
   const int i1 = j / q, i2 = j - i1 * q;
   const bool sampled = (i1 % d == 0) && (i2 % d == 0);
-  // p1mode 1: a basis couples the sampled pixels across bands (p1_subspace_kernel);
-  // p1mode 2: fused-S splitting, no P1
-  const int p1mode = S.fused ? 2 : (S.subspace ? 1 : 0);
-  const bool p1 = !(p1mode == 2 || (sampled && p1mode == 1));
+  // no P1 with the fused-S splitting; with a basis p1_subspace_kernel updates the sampled
+  // pixels; and with W1 in place of B X the others hold their W1 (see launch_pupdate)
+  const bool p1 = !S.fused && (sampled ? !S.subspace : bx_s != w1_s);
   const size_t lplane = (size_t)(p / d) * (q / d), lj = (size_t)(i1 / d) * (q / d) + i2 / d;
   float xs[KEEP ? kPuKeep : 1], l2s[KEEP ? kPuKeep : 1], bxs[KEEP ? kPuKeep : 1],
       l1s[KEEP ? kPuKeep : 1], yls[KEEP ? kPuKeep : 1], yh[LHM];
@@ -970,14 +976,14 @@ pupdate_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
   if constexpr (KEEP)
     pupdate_write_kept<LHM>(xs, l2s, bxs, l1s, yls, gslot<gfloat>(S, l1o_s),
                             gslot<gfloat>(S, l2o_s), gslot<gfloat>(S, w1_s),
-                            gslot<gfloat>(S, w2_s), R, u, plane, sampled, p1mode, Lh, S.rho,
-                            S.inv_1prho, c0, c1, j);
+                            gslot<gfloat>(S, w2_s), gslot<gfloat>(S, bxo_s), R, u, plane,
+                            sampled, p1, Lh, S.rho, S.inv_1prho, c0, c1, j);
   else
     pupdate_write<LHM>(X, gslot<const gfloat>(S, bx_s), gslot<const gfloat>(S, yl_s),
                        gslot<const gfloat>(S, l1_s), L2, gslot<gfloat>(S, l1o_s),
                        gslot<gfloat>(S, l2o_s), gslot<gfloat>(S, w1_s), gslot<gfloat>(S, w2_s),
-                       R, u, plane, lplane, lj, sampled, p1mode, Lh, S.rho, S.inv_1prho, c0, c1,
-                       j);
+                       gslot<gfloat>(S, bxo_s), R, u, plane, lplane, lj, sampled, p1, Lh, S.rho,
+                       S.inv_1prho, c0, c1, j);
 }
 
 template <typename Kern, typename... Args>
@@ -1194,33 +1200,33 @@ int launch_conv(const Batch& B, int in, int out, bool transpose, int add1, int a
 
 template <int LHM, int NC>
 void launch_pu(const Batch& B, const Group& g, int x, int bx, int yl, int yh, int l1, int l2,
-               int w1, int w2, int l1o, int l2o, hipStream_t s) {
+               int w1, int w2, int l1o, int l2o, int bxo, hipStream_t s) {
   int maxL = 0;
   for (const auto& P : B.scenes) maxL = std::max(maxL, P->Lx);
   if (maxL <= kPuKeep * NC)
     hipLaunchKernelGGL((pupdate_kernel<LHM, NC, true>), dim3(g.nitems), dim3(256 * NC), 0, s,
-                       B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o);
+                       B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
   else
     hipLaunchKernelGGL((pupdate_kernel<LHM, NC, false>), dim3(g.nitems), dim3(256 * NC), 0, s,
-                       B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o);
+                       B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
 }
 
 int launch_pupdate(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1, int w2,
-                   int l1o, int l2o, hipStream_t s) {
+                   int l1o, int l2o, int bxo, hipStream_t s) {
   // one launch per guide-band class (key0 = 1, 4 or 16 register slots) and threads per
   // pixel (key1 = 1 or 4)
   for (const Group& g : B.groups[KD_PIXEL]) {
     if (!g.nitems) continue;
     const bool split = g.key1 == 4;
     if (g.key0 == 1) {
-      if (split) launch_pu<1, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, s);
-      else launch_pu<1, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, s);
+      if (split) launch_pu<1, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
+      else launch_pu<1, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
     } else if (g.key0 == 4) {
-      if (split) launch_pu<4, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, s);
-      else launch_pu<4, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, s);
+      if (split) launch_pu<4, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
+      else launch_pu<4, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
     } else {
-      if (split) launch_pu<kMaxLh, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, s);
-      else launch_pu<kMaxLh, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, s);
+      if (split) launch_pu<kMaxLh, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
+      else launch_pu<kMaxLh, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
     }
     NLPR_LAUNCH_CHECK("pupdate_kernel");
   }

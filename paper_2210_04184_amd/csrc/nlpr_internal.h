@@ -51,12 +51,11 @@ enum Slot {
   B_GZ,      // Z' (input)
   B_GC,      // C'
   B_GCP,     // C' of the backward step before (the sweep adjoint rebuilds Sigma'' from it)
-  B_GL1, B_GL2,   // Lambda1'', Lambda2''
+  B_GL1,     // Lambda1'' (sampled pixels)
   B_GSIG,    // Sigma'' (coded: float4 items with an element inside the threshold, packed)
   B_GX,      // X'
-  B_GW1,     // W1' = B C'
-  B_GBX,     // BX'
-  B_GXP,     // X' of the P-update
+  B_GW1,     // W1' = B C', then BX' (they differ on the sampled pixels)
+  B_GXP,     // X' of the P-update, which is also -Lambda2''
   B_GXR,     // X' of the sweep (+ halo rows in B_GHALO)
   B_GHALO,
   B_GMUP,    // mu' partial tiles [L][ntiles][Npairs][R + 2K][q]
@@ -311,9 +310,11 @@ int launch_init(const Batch& B, int yl, int ylp, int x0, int l1, int l2, int w2,
 int launch_conv(const Batch& B, int in, int out, bool transpose, int add1, int add2, int halo,
                 int reg_mask, hipStream_t s);
 // Lambda1, Lambda2 are read from slots l1, l2 and written to l1o, l2o (the same slots for an
-// update in place)
+// update in place).  bx == w1: B X lies in W1 and only the sampled pixels' P1, Lambda1 and W1
+// are updated, the others being P1 + Lambda1 = B X with Lambda1 = 0 already.  bxo >= 0: the slot
+// that also takes B X where P1 is updated.
 int launch_pupdate(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1, int w2,
-                   int l1o, int l2o, hipStream_t s);
+                   int l1o, int l2o, int bxo, hipStream_t s);
 // Re-point buffer slots of the descriptor of scene 0 on the stream: kernels enqueued after it
 // see the new buffers.  The reverse-mode passes move through their checkpoints this way.
 struct SlotSet {
@@ -358,8 +359,7 @@ int launch_sweep_bwd(const Batch& B, int cb, const uint8_t* codes, int sb, int x
                      int mup, const uint8_t* pcodes, int cbp, hipStream_t s);
 int launch_mubar_reduce(const Batch& B, int mup, int mub, hipStream_t s);
 int launch_pupdate_bwd(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1b,
-                       int w2b, int l1b, int l2b, int bxb, int xp, int gyl, int gyh, int part,
-                       hipStream_t s);
+                       int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s);
 int launch_weights_bwd(const Batch& B, int yh, int mub, int eb, int part, int w0, hipStream_t s);
 int launch_yh_bwd(const Batch& B, int yh, int eb, int gyh, hipStream_t s);
 int launch_upsample_bwd(const Batch& B, int x0b, int gyl, hipStream_t s);

@@ -20,28 +20,7 @@ __device__ __forceinline__ int wrapg(int a, int m) {
   a %= m;
   return a < 0 ? a + m : a;
 }
-// Sum of v[k] over the NW waves of the workgroup, in a fixed order; thread 0 gets it.
-template <int N, int NW>
-__device__ __forceinline__ void block_sum_waves(double (&v)[N]) {
-  __shared__ double red[N][NW];
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_down(v[k], off, 64);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0)
-#pragma unroll
-    for (int k = 0; k < N; ++k) red[k][w] = v[k];
-  __syncthreads();
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      double a = 0.0;
-      for (int i = 0; i < NW; ++i) a += red[k][i];
-      v[k] = a;
-    }
-  __syncthreads();
-}
-
+// Sum of v[k] over the 4 waves of the workgroup, in a fixed order; thread 0 gets it.
 template <int N>
 __device__ __forceinline__ void block_sum256(double (&v)[N]) {
   __shared__ double red[N][4];
@@ -398,7 +377,7 @@ sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ item
 __global__ void __launch_bounds__(256)
 mubar_reduce_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int mup_s,
                     int mub_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, R = S.rows, ntiles = S.ntiles, ER = S.rows + 2 * S.K;
   const size_t plane = (size_t)p * q;
@@ -426,8 +405,8 @@ mubar_reduce_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ i
 // the bands.  Inputs: X, BX of the iteration, Y_l,
 // Y_h, Lambda1 and Lambda2 before the update; adjoints W1' (= B C'), W2' (= C'), Lambda1'',
 // Lambda2'' of the outputs.  Outputs: BX', X' of this step, Lambda'' of the inputs (in
-// place), Y_l' and Y_h' accumulated, and per workgroup two FP64 partial sums of rho', added
-// to the workgroup's own slot (repeatable across iterations): through P1, and through G,
+// place), Y_l' and Y_h' accumulated, and per workgroup (256 pixels / NC) two FP64 partial sums
+// of rho', added to the workgroup's own slot (repeatable across iterations): through P1, and through G,
 // where G' = sum res s^T and dG/drho = -G G / lambda1 give -res^T G (G s) / lambda1 per
 // pixel.  The band sums res = Y_h - A0 R and s = P2' R are formed per share and added in
 // LDS in a fixed order.
@@ -523,20 +502,22 @@ __device__ __forceinline__ double pupdate_bwd_write_kept(
 // arithmetic and its order are those of the band loops.
 constexpr int kPbKeep = 8;
 template <int LHM, int PB_NC, bool KEEP>
-__global__ void __launch_bounds__(256 * PB_NC)
+__global__ void __launch_bounds__(256)
 pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                    int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1b_s, int w2b_s,
                    int l1b_s, int xp_s, int gyl_s, int gyh_s, int part_s) {
-  __shared__ float part[PB_NC > 1 ? PB_NC : 1][PB_NC > 1 ? LHM : 1][PB_NC > 1 ? 256 : 1];
-  const int2 it = items[blockIdx.x];
+  constexpr int PX = 256 / PB_NC;          // pixels of the workgroup
+  __shared__ float part[PB_NC > 1 ? PB_NC : 1][PB_NC > 1 ? LHM : 1][PB_NC > 1 ? PX : 1];
+  const int2 it = work_item(items, blockIdx.x / PB_NC);
+  const int sub = blockIdx.x % PB_NC;
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, L = S.L, Lh = S.Lh, d = S.d;
   const size_t plane = (size_t)p * q;
-  // the band share is uniform over a wave (256 threads per share); readfirstlane lets the
-  // band loops index R and G with scalar loads
-  const int pix = threadIdx.x & 255;
-  const int ch = PB_NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-  const int j = it.y * 256 + pix;
+  // the band share is uniform over a wave; readfirstlane lets the band loops index R and G
+  // with scalar loads
+  const int pix = threadIdx.x & (PX - 1);
+  const int ch = PB_NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PX);
+  const int j = it.y * 256 + sub * PX + pix;
   const bool act = j < (int)plane;
   const int c0 = (L * ch) / PB_NC, c1 = (L * (ch + 1)) / PB_NC;
   const gfloat* X = gslot<const gfloat>(S, x_s);
@@ -667,9 +648,9 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
       acc[0] = pupdate_bwd_write<LHM>(BX, Yl, L1, W1b, W2b, L1b, Xp, GYl, R, v, plane,
                                       lplane, lj, sampled, Lh, inv, rr, c0, c1, j);
   }
-  block_sum_waves<2, 4 * PB_NC>(acc);
+  block_sum256<2>(acc);
   if (threadIdx.x == 0) {
-    gdouble* prt = gslot<gdouble>(S, part_s) + 2 * (size_t)it.y;
+    gdouble* prt = gslot<gdouble>(S, part_s) + 2 * ((size_t)it.y * PB_NC + sub);
     prt[0] += acc[0];
     prt[1] += acc[1];
   }
@@ -687,7 +668,7 @@ __global__ void __launch_bounds__(256)
 weights_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int yh_s,
                    int mub_s, int eb_s, int part_s, int w0) {
   extern __shared__ float wsh[];
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, K = S.K, Lh = S.Lh;
   const int gx = ceil_div(q, WB_X), gy = ceil_div(p, WB_Y);
@@ -779,7 +760,7 @@ weights_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
 __global__ void __launch_bounds__(256)
 yh_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int yh_s,
               int eb_s, int gyh_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q;
   const size_t plane = (size_t)p * q;
@@ -807,7 +788,7 @@ yh_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, 
 __global__ void __launch_bounds__(256)
 upsample_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x0b_s,
                     int gyl_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, d = S.d, pd = S.p / S.d, qd = S.q / S.d;
   const size_t e = (size_t)it.y * 256 + threadIdx.x;
@@ -848,7 +829,7 @@ int launch_kind(const Batch& B, Kind kind, const char* name, Kern kern, hipStrea
                 Args... args) {
   for (const Group& g : B.groups[kind]) {
     if (g.nitems == 0) continue;
-    hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(256), g.lds, s, B.d_desc, g.d_items, args...);
+    hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(256), g.lds, s, B.d_desc, items_of(B, g), args...);
     NLPR_LAUNCH_CHECK(name);
   }
   return NLPR_OK;
@@ -941,6 +922,12 @@ int launch_sweep_bwd(const Batch& B, int cb, const uint8_t* codes, int sb, int x
   return NLPR_OK;
 }
 
+// Threads per pixel, and with them workgroups and partial sums per work item.
+int pupdate_bwd_split(const Plan& P) {
+  if (pixel_split((size_t)P.prm.p * P.prm.q) != 4) return 1;
+  return lh_class(P.prm.Lh) == kMaxLh ? 2 : 4;       // registers: 2 at most
+}
+
 int launch_mubar_reduce(const Batch& B, int mup, int mub, hipStream_t s) {
   return launch_kind(B, KD_MUPLANE, "mubar_reduce_kernel", mubar_reduce_kernel, s, mup, mub);
 }
@@ -950,12 +937,12 @@ void launch_pb(const Batch& B, const Group& g, int x, int bx, int yl, int yh, in
                int w1b, int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s) {
   // the reverse mode takes one scene: its bands per thread decide the variant
   if (ceil_div(B.scenes[0]->Lx, NC) <= kPbKeep)
-    hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, true>), dim3(g.nitems), dim3(256 * NC), 0,
-                       s, B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
+    hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, true>), dim3(g.nitems * NC), dim3(256), 0,
+                       s, B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
                        gyl, gyh, part);
   else
-    hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, false>), dim3(g.nitems), dim3(256 * NC), 0,
-                       s, B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
+    hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, false>), dim3(g.nitems * NC), dim3(256), 0,
+                       s, B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
                        gyl, gyh, part);
 }
 
@@ -987,7 +974,7 @@ int launch_weights_bwd(const Batch& B, int yh, int mub, int eb, int part, int w0
 int launch_yh_bwd(const Batch& B, int yh, int eb, int gyh, hipStream_t s) {
   for (const Group& g : B.groups[KD_PIXEL]) {
     if (!g.nitems) continue;
-    hipLaunchKernelGGL(yh_bwd_kernel, dim3(g.nitems), dim3(256), 0, s, B.d_desc, g.d_items, yh,
+    hipLaunchKernelGGL(yh_bwd_kernel, dim3(g.nitems), dim3(256), 0, s, B.d_desc, items_of(B, g), yh,
                        eb, gyh);
     NLPR_LAUNCH_CHECK("yh_bwd_kernel");
   }

@@ -866,7 +866,7 @@ GradLayout grad_layout(const Plan& P) {
   };
   for (int k : {B_GC, B_GCP, B_GL1, B_GX, B_GW1, B_GXP, B_GXR}) take(k, pl);
   const size_t mup = (size_t)P.npairs * P.prm.p * P.prm.q * sizeof(float);
-  G.npix = pixel_blocks(P);
+  G.npix = pixel_blocks(P) * pupdate_bwd_split(P);
   G.nw = P.npairs ? weights_bwd_blocks(P) : 0;
   take(B_GSIG, P.sz[B_SIGMA]);
   take(B_GHALO, P.sz[B_HALO]);

@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(256) subspace_kernel(const float* E, const flo
 __global__ void __launch_bounds__(256)
 project_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int yl_s,
                int yle_s, int ylp_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int nl = (S.p / S.d) * (S.q / S.d);
   const int m = it.y * 256 + threadIdx.x;
@@ -283,7 +283,7 @@ project_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
 __global__ void __launch_bounds__(256)
 p1_subspace_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int bx_s,
                    int yle_s, int l1_s, int w1_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int qd = S.q / S.d;
   const int nl = (S.p / S.d) * qd;
@@ -328,7 +328,7 @@ p1_subspace_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
 __global__ void __launch_bounds__(256)
 compose_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                int z_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const size_t plane = (size_t)S.p * S.q;
   const int j = it.y * 256 + threadIdx.x;
@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(256)
 weights_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int yh_s,
                int mu_s) {
   extern __shared__ float wsh[];
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, K = S.K, Lh = S.Lh;
   const int gx = ceil_div(q, WT_X), gy = ceil_div(p, WT_Y);
@@ -412,7 +412,7 @@ weights_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
 __global__ void __launch_bounds__(256)
 init_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int yl_s, int ylp_s,
             int x0_s, int l1_s, int l2_s, int w2_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, d = S.d;
   const size_t e = (size_t)it.y * 256 + threadIdx.x;
@@ -433,7 +433,7 @@ init_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, in
 __global__ void __launch_bounds__(256)
 upsample_zero_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int yl_s,
                      int t_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, d = S.d;
   const size_t e = (size_t)it.y * 256 + threadIdx.x;
@@ -449,7 +449,7 @@ upsample_zero_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ 
 
 __global__ void __launch_bounds__(256)
 fill_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int s_) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const size_t e = (size_t)it.y * 256 + threadIdx.x;
   if (e < (size_t)S.L * S.p * S.q) gslot<gfloat>(S, s_)[e] = 0.f;
@@ -461,7 +461,7 @@ fill_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, in
 __global__ void __launch_bounds__(256)
 finite_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int z_s,
               int* flag, int iter) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const size_t e = (size_t)it.y * 256 + threadIdx.x;
   if (e < (size_t)S.L * S.p * S.q && !isfinite(gslot<const gfloat>(S, z_s)[e]))
@@ -503,7 +503,7 @@ conv_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, in
             int add1_s, int add2_s, int halo_s, int reg_mask) {
   extern __shared__ float4 csh4[];           // 16-byte aligned: the rank-one pass stores float4
   float* csh = reinterpret_cast<float*>(csh4);
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item_xcd(items);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, r = S.r;
   const int gx = ceil_div(q, CV_X), gy = ceil_div(p, CV_Y);
@@ -716,9 +716,10 @@ conv_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, in
 }
 
 // ---------------------------------------------------------------------------- pupdate
-// Work item = 256 pixels; a workgroup of 256 NC threads gives each pixel NC threads (1, or
-// 4 when the launch covers few pixels in all, so that it still fills the GPU), each owning
-// a contiguous share of the bands.
+// Work item = 256 pixels.  A pixel has NC threads (1, or 4 when the launch covers few pixels in
+// all, so that it still fills the GPU), each owning a contiguous share of the bands; with 4 a
+// workgroup takes a quarter of the item's pixels, one wave per share, so that the exchange of
+// the shares holds up four waves instead of sixteen.
 // With E = I:
 //   P1 = (rho BX + Y_l - rho Lambda1) / (1 + rho)  on sampled pixels (S^T S = 1)
 //   P1 = BX - Lambda1                              elsewhere            (eq. (Qh_update))
@@ -878,19 +879,20 @@ __device__ __forceinline__ void pupdate_write_kept(
 }
 
 template <int LHM, int PU_NC, bool KEEP>
-__global__ void __launch_bounds__(256 * PU_NC)
+__global__ void __launch_bounds__(256)
 pupdate_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1_s, int w2_s, int l1o_s,
                int l2o_s, int bxo_s) {
-  __shared__ float part[PU_NC > 1 ? PU_NC : 1][PU_NC > 1 ? LHM : 1][PU_NC > 1 ? 256 : 1];
-  const int2 it = items[blockIdx.x];
+  constexpr int PX = 256 / PU_NC;          // pixels of the workgroup
+  __shared__ float part[PU_NC > 1 ? PU_NC : 1][PU_NC > 1 ? LHM : 1][PU_NC > 1 ? PX : 1];
+  const int2 it = work_item(items, blockIdx.x / PU_NC);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, L = S.L, Lh = S.Lh, d = S.d;
-  // the band share is uniform over a wave (256 threads per share); readfirstlane lets the
-  // band loops index R and G with scalar loads
-  const int pix = threadIdx.x & 255;
-  const int ch = PU_NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-  const int j = it.y * 256 + pix;
+  // the band share is uniform over a wave; readfirstlane lets the band loops index R and G
+  // with scalar loads
+  const int pix = threadIdx.x & (PX - 1);
+  const int ch = PU_NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PX);
+  const int j = it.y * 256 + (blockIdx.x % PU_NC) * PX + pix;
   const size_t plane = (size_t)p * q;
   const bool act = j < (int)plane;
   const int c0 = (L * ch) / PU_NC, c1 = (L * (ch + 1)) / PU_NC;   // this thread's bands
@@ -991,7 +993,7 @@ int launch_groups(const Batch& B, Kind kind, const char* name, Kern kern, hipStr
                   Args... args) {
   for (const Group& g : B.groups[kind]) {
     if (g.nitems == 0) continue;
-    hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc, g.d_items,
+    hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc, items_of(B, g),
                        args...);
     NLPR_LAUNCH_CHECK(name);
   }
@@ -1173,7 +1175,7 @@ template <int RM>
 int launch_conv_rm(const Group& g, const Batch& B, int in, int out, bool transpose, int add1,
                    int add2, int halo, int reg_mask, hipStream_t s) {
   auto kern = transpose ? conv_kernel<true, RM> : conv_kernel<false, RM>;
-  hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(256), g.lds, s, B.d_desc, g.d_items, in, out, add1,
+  hipLaunchKernelGGL(kern, dim3(g.nitems), dim3(256), g.lds, s, B.d_desc, items_of(B, g), in, out, add1,
                      add2, halo, reg_mask);
   NLPR_LAUNCH_CHECK("conv_kernel");
   return NLPR_OK;
@@ -1204,11 +1206,11 @@ void launch_pu(const Batch& B, const Group& g, int x, int bx, int yl, int yh, in
   int maxL = 0;
   for (const auto& P : B.scenes) maxL = std::max(maxL, P->Lx);
   if (maxL <= kPuKeep * NC)
-    hipLaunchKernelGGL((pupdate_kernel<LHM, NC, true>), dim3(g.nitems), dim3(256 * NC), 0, s,
-                       B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
+    hipLaunchKernelGGL((pupdate_kernel<LHM, NC, true>), dim3(g.nitems * NC), dim3(256), 0, s,
+                       B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
   else
-    hipLaunchKernelGGL((pupdate_kernel<LHM, NC, false>), dim3(g.nitems), dim3(256 * NC), 0, s,
-                       B.d_desc, g.d_items, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
+    hipLaunchKernelGGL((pupdate_kernel<LHM, NC, false>), dim3(g.nitems * NC), dim3(256), 0, s,
+                       B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
 }
 
 int launch_pupdate(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1, int w2,

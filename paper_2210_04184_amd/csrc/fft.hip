@@ -214,7 +214,7 @@ __device__ __forceinline__ int row_pos(int i) { return i + (i >> 3); }
 __global__ void fft_rows_fwd(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
                              int c_s, int f_s) {
   extern __shared__ float2 sh[];
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item_xcd(items);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, L = S.L, lpb = S.fq_lpb, tpl = S.fq_tpl;
   const int nrb = ceil_div(p, lpb);
@@ -354,7 +354,7 @@ __device__ __forceinline__ void cols_from_lds(const SceneDesc& S, int t, int tpl
 __global__ void fft_cols_solve(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
                                int f_s) {
   extern __shared__ float2 sh[];
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item_xcd(items);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, cb = S.fp_cb, tpl = S.fp_tpl;
   const int ncb = ceil_div(q, cb);
@@ -438,7 +438,7 @@ template <bool ADD>
 __global__ void fft_rows_inv(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
                              int f_s, int x_s, int add_s) {
   extern __shared__ float2 sh[];
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item_xcd(items);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, L = S.L, lpb = S.fq_lpb, tpl = S.fq_tpl;
   const int nrb = ceil_div(p, lpb);
@@ -488,13 +488,13 @@ int launch_rows(const Batch& B, bool inv, int a, int b, int add, hipStream_t s) 
     if (!g.nitems) continue;
     if (inv && add >= 0)
       hipLaunchKernelGGL(fft_rows_inv<true>, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
-                         g.d_items, a, b, add);
+                         items_of(B, g), a, b, add);
     else if (inv)
       hipLaunchKernelGGL(fft_rows_inv<false>, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
-                         g.d_items, a, b, -1);
+                         items_of(B, g), a, b, -1);
     else
       hipLaunchKernelGGL(fft_rows_fwd, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
-                         g.d_items, a, b);
+                         items_of(B, g), a, b);
     NLPR_LAUNCH_CHECK(inv ? "fft_rows_inv" : "fft_rows_fwd");
   }
   return NLPR_OK;
@@ -504,7 +504,7 @@ int launch_cols(const Batch& B, int f, hipStream_t s) {
   for (const Group& g : B.groups[KD_COLS]) {
     if (!g.nitems) continue;
     hipLaunchKernelGGL(fft_cols_solve, dim3(g.nitems), dim3(g.block), g.lds, s, B.d_desc,
-                       g.d_items, f);
+                       items_of(B, g), f);
     NLPR_LAUNCH_CHECK("fft_cols_solve");
   }
   return NLPR_OK;

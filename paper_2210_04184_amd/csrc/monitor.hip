@@ -48,7 +48,7 @@ __device__ __forceinline__ void block_sum(double (&v)[N]) {
 __global__ void __launch_bounds__(256)
 monitor_pixel_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                      int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1_s, int w2_s) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, L = S.L, Lh = S.Lh, d = S.d;
   const size_t plane = (size_t)p * q;
@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(256)
 monitor_reg_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
                    int mu_s) {
   extern __shared__ float msh[];
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, K = S.K, L = S.L;
   const int gx = ceil_div(q, MR_X), gy = ceil_div(p, MR_Y);
@@ -180,7 +180,7 @@ monitor_reg_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
 __global__ void __launch_bounds__(256)
 monitor_reduce_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items,
                       int point, int iter) {
-  const int2 it = items[blockIdx.x];
+  const int2 it = work_item(items, blockIdx.x);
   const SceneDesc& S = sd[it.x];
   const gdouble* part = (const gdouble*)S.mon;
   double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -220,20 +220,20 @@ int launch_monitor(const Batch& B, int point, int iter, hipStream_t s) {
   for (const Group& g : B.groups[KD_PIXEL]) {
     if (!g.nitems) continue;
     hipLaunchKernelGGL(monitor_pixel_kernel, dim3(g.nitems), dim3(256), 0, s, B.d_desc,
-                       g.d_items, (int)B_Z, (int)B_BX, (int)B_YL, (int)B_YH, (int)B_L1,
+                       items_of(B, g), (int)B_Z, (int)B_BX, (int)B_YL, (int)B_YH, (int)B_L1,
                        (int)B_L2, (int)B_W1, (int)B_W2);
     NLPR_LAUNCH_CHECK("monitor_pixel_kernel");
   }
   for (const Group& g : B.groups[KD_MONREG]) {
     if (!g.nitems) continue;
     hipLaunchKernelGGL(monitor_reg_kernel, dim3(g.nitems), dim3(256), g.lds, s, B.d_desc,
-                       g.d_items, (int)B_Z, (int)B_MU);
+                       items_of(B, g), (int)B_Z, (int)B_MU);
     NLPR_LAUNCH_CHECK("monitor_reg_kernel");
   }
   for (const Group& g : B.groups[KD_SCENE]) {
     if (!g.nitems) continue;
     hipLaunchKernelGGL(monitor_reduce_kernel, dim3(g.nitems), dim3(256), 0, s, B.d_desc,
-                       g.d_items, point, iter);
+                       items_of(B, g), point, iter);
     NLPR_LAUNCH_CHECK("monitor_reduce_kernel");
   }
   return NLPR_OK;

@@ -217,6 +217,11 @@ struct Batch {
   int64_t acc_n[NLPR_STAGE_COUNT] = {};
 };
 
+// The work-item table a launch passes (work_item): none for a single scene.
+inline const int2* items_of(const Batch& B, const Group& g) {
+  return B.scenes.size() == 1 ? nullptr : g.d_items;
+}
+
 // ---- error plumbing (api.hip)
 void set_error(const std::string& msg);
 #define NLPR_HIP_TRY(expr)                                                          \
@@ -278,6 +283,17 @@ __device__ __forceinline__ float4 ldg4(const gfloat* p) {
 __device__ __forceinline__ void stg4(gfloat* p, float4 a) {
   const v4f_t v = {a.x, a.y, a.z, a.w};
   *(gv4f*)p = v;
+}
+// A workgroup's work item.  The launches of a single scene need no table (items is null): the
+// scene is 0 and the local block is the workgroup index, or, where the table is ordered by
+// XCD, the same position of that order (xcd_append from position 0).  A table costs a dependent
+// load in front of everything a kernel does, which is most of a microsecond of a launch.
+__device__ __forceinline__ int2 work_item(const int2* items, unsigned b) {
+  return items ? items[b] : make_int2(0, (int)b);
+}
+__device__ __forceinline__ int2 work_item_xcd(const int2* items) {
+  const unsigned b = blockIdx.x, n = gridDim.x, x = b & 7u;
+  return items ? items[b] : make_int2(0, (int)(x * (n >> 3) + min(x, n & 7u) + (b >> 3)));
 }
 __device__ __forceinline__ int2 tau_at(const SceneDesc& S, int n) {
   const v2i_t v = ((const gv2i*)S.taus)[n];
@@ -357,6 +373,7 @@ int sweep_bwd_prepare(int K);
 // first backward step, whose incoming Sigma'' is zero)
 int launch_sweep_bwd(const Batch& B, int cb, const uint8_t* codes, int sb, int xr, int halo,
                      int mup, const uint8_t* pcodes, int cbp, hipStream_t s);
+int pupdate_bwd_split(const Plan& P);
 int launch_mubar_reduce(const Batch& B, int mup, int mub, hipStream_t s);
 int launch_pupdate_bwd(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1b,
                        int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s);

@@ -13,6 +13,7 @@
 #include <cmath>
 
 #include <climits>
+#include <cstring>
 
 #include "nlpr_internal.h"
 
@@ -1006,6 +1007,16 @@ __global__ void set_slots_kernel(SceneDesc* sd, SlotSet set) {
   if (i < set.n) sd->buf[set.slot[i]] = set.ptr[i];
 }
 
+// Descriptor 0 written from the kernel argument, one word per thread.
+struct DescWords {
+  static_assert(sizeof(SceneDesc) % 4 == 0, "whole words");
+  unsigned w[sizeof(SceneDesc) / 4];
+};
+__global__ void __launch_bounds__(256) set_desc_kernel(SceneDesc* sd, DescWords d) {
+  for (unsigned i = threadIdx.x; i < sizeof(SceneDesc) / 4; i += 256)
+    reinterpret_cast<unsigned*>(sd)[i] = d.w[i];
+}
+
 // Reference stream with the sweep's access shape and none of its arithmetic: workgroup b owns chunk
 // (b mod bands) * per_band + b / bands of chunk4 float4s and negates it in place, P planes of
 // 256 float4 (4 KB) at a time, all loads of a step before its stores.  The dynamic LDS the
@@ -1105,6 +1116,14 @@ int launch_set_slots(const Batch& B, const SlotSet& set, hipStream_t s) {
   if (set.n <= 0) return NLPR_OK;
   hipLaunchKernelGGL(set_slots_kernel, dim3(1), dim3(64), 0, s, B.d_desc, set);
   NLPR_LAUNCH_CHECK("set_slots_kernel");
+  return NLPR_OK;
+}
+
+int launch_set_desc(const Batch& B, const SceneDesc& d, hipStream_t s) {
+  DescWords w;
+  std::memcpy(w.w, &d, sizeof(d));
+  hipLaunchKernelGGL(set_desc_kernel, dim3(1), dim3(256), 0, s, B.d_desc, w);
+  NLPR_LAUNCH_CHECK("set_desc_kernel");
   return NLPR_OK;
 }
 

@@ -130,6 +130,7 @@ struct FftShape {
 // One scene: parameters, device tables and its part of the workspace.
 struct Plan {
   nlpr_params prm{};
+  void* arena = nullptr;          // the device tables below, one allocation
   int npairs = 0;
   int npatch = 0;
   std::vector<int32_t> taus;      // W+ (tau1, tau2 pairs)
@@ -161,8 +162,10 @@ struct Plan {
 };
 
 // A launch: the work items of the scenes that share its template parameters.
+constexpr size_t kNoTable = ~size_t(0);
 struct Group {
-  int2* d_items = nullptr;
+  const int2* d_items = nullptr;   // the work items, in the batch's arena
+  size_t table = kNoTable;         // and where they start there
   int nitems = 0;
   int block = 256;
   size_t lds = 0;
@@ -194,8 +197,10 @@ struct Batch {
   std::vector<Plan*> scenes;       // owned
   std::vector<size_t> base;        // workspace base of each scene
   size_t ws_bytes = 0;
+  void* arena = nullptr;           // work-item tables, descriptors, flag, counters
+  std::vector<int2> tables;        // the tables while the batch is built
   SceneDesc* d_desc = nullptr;     // device descriptors, one per scene
-  SceneDesc* h_desc = nullptr;     // pinned staging copy
+  SceneDesc* h_desc = nullptr;     // pinned staging copy (more than one scene)
   std::vector<SceneDesc> uploaded; // what d_desc holds
   bool desc_valid = false;
   hipEvent_t upload_ev = nullptr;
@@ -342,6 +347,7 @@ struct SlotSet {
   }
 };
 int launch_set_slots(const Batch& B, const SlotSet& set, hipStream_t s);
+int launch_set_desc(const Batch& B, const SceneDesc& d, hipStream_t s);   // scene 0's descriptor
 int lh_class(int Lh);                // pupdate template class of a guide-band count: 1, 4 or 16
 // threads per pixel of a P-update launch over `pixels` pixels in all: 4 (bands split) below
 // 131072, where one thread per pixel would leave most of the GPU idle, else 1

@@ -581,7 +581,9 @@ int batch_build(Batch& B) {
     pbands += (size_t)P->prm.p * P->prm.q * P->Lx;
     reg = reg || P->npairs > 0;
   }
-  if (reg && !B.timing && pbands >= kForkPixelBands) {
+  const Plan& P0 = *B.scenes[0];
+  const bool one = sweep_pu(B) && !P0.d_E && (size_t)P0.prm.p * P0.prm.q < kForkPixels;
+  if (reg && !B.timing && pbands >= kForkPixelBands && !one) {
     NLPR_HIP_TRY(hipStreamCreateWithFlags(&B.side, hipStreamNonBlocking));
     NLPR_HIP_TRY(hipEventCreateWithFlags(&B.fork_ev, hipEventDisableTiming));
     NLPR_HIP_TRY(hipEventCreateWithFlags(&B.join_ev, hipEventDisableTiming));
@@ -730,19 +732,25 @@ int enqueue_solve(Batch& B, bool resume, hipStream_t s) {
       StageTimer tm(B, sp, NLPR_STAGE_BLUR);
       if ((rc = launch_conv(B, B_Z, bx, false, -1, -1, -1, 0, sp))) return rc;
     }
-    {
+    const bool first = t == 0 && !resume;
+    const PuSlots pu{B_Z, bx, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, -1};
+    const bool both = reg && !mon && !first && sweep_pu(B);   // in one launch
+    if (both) {
+      if ((rc = launch_sweep_pu(B, pu, B_Z, B_MU, B_SIGMA, B_C, B_HALO, s, nullptr))) return rc;
+    } else {
       StageTimer tm(B, sp, NLPR_STAGE_PUPDATE);
-      if ((rc = launch_pupdate(B, B_Z, bx, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, -1, sp)))
-        return rc;
-      if (sub && (rc = launch_p1_subspace(B, bx, B_YLE, B_L1, B_W1, sp))) return rc;
+      if ((rc = launch_pupdate(B, pu, sp))) return rc;
+    }
+    if (sub) {
+      StageTimer tm(B, sp, NLPR_STAGE_PUPDATE);
+      if ((rc = launch_p1_subspace(B, bx, B_YLE, B_L1, B_W1, sp))) return rc;
     }
     if (tpart && (rc = launch_conv(B, B_W1, B_BX, true, B_W2, -1, -1, 0, sp))) return rc;
     if (mon) {
       StageTimer tm(B, s, NLPR_STAGE_MONITOR);
       if ((rc = launch_monitor(B, point++, t + 1, s))) return rc;
     }
-    if (reg) {
-      const bool first = (t == 0 && !resume);
+    if (reg && !both) {
       StageTimer tm(B, s, first ? NLPR_STAGE_SWEEP_FIRST : NLPR_STAGE_SWEEP);
       if ((rc = launch_sweep(B, B_Z, B_MU, B_SIGMA, B_C, B_HALO, first, s, nullptr,
                              B.d_counts ? B.d_counts + (size_t)t * kCountSlots * kCountStride
@@ -987,11 +995,15 @@ int grad_forward(Batch& B, const float* Yl, const float* Yh, float* Z, void* ws,
     if ((rc = launch_xsolve(B, B_C, B_Z, B_F, -1, s))) return rc;
     if (t == T) break;
     if ((rc = launch_conv(B, B_Z, B_W1, false, -1, -1, -1, 0, s))) return rc;
-    if ((rc = launch_pupdate(B, B_Z, B_W1, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1O, B_L2O, B_BX, s)))
-      return rc;
-    if (reg && (rc = launch_sweep(B, B_Z, B_MU, B_SIGMA, B_C, B_HALO, t == 1, s,
-                                  ck_codes(ck, G, T, t))))
-      return rc;
+    const PuSlots pu{B_Z, B_W1, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1O, B_L2O, B_BX};
+    uint8_t* codes = ck_codes(ck, G, T, t);
+    if (reg && t > 1 && sweep_pu(B)) {
+      if ((rc = launch_sweep_pu(B, pu, B_Z, B_MU, B_SIGMA, B_C, B_HALO, s, codes))) return rc;
+    } else {
+      if ((rc = launch_pupdate(B, pu, s))) return rc;
+      if (reg && (rc = launch_sweep(B, B_Z, B_MU, B_SIGMA, B_C, B_HALO, t == 1, s, codes)))
+        return rc;
+    }
     if ((rc = launch_conv(B, B_W1, B_C, true, B_W2, B_C, B_HALO, 2 | 4, s))) return rc;
   }
   NLPR_HIP_TRY(hipEventRecord(B.done_ev, s));
@@ -1446,7 +1458,8 @@ int nlpr_debug_stage(nlpr_plan* plan, int stage, void* const* bufs, int32_t nbuf
       put(B_Z, 0); put(B_BX, 1); put(B_YL, 2); put(B_YH, 3); put(B_L1, 4); put(B_L2, 5);
       put(B_W1, 6); put(B_W2, 7);
       return run([&] {
-        return launch_pupdate(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, -1, s);
+        return launch_pupdate(
+            B, PuSlots{B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_W1, B_W2, B_L1, B_L2, -1}, s);
       });
     case NLPR_STAGE_SWEEP:
     case NLPR_STAGE_SWEEP_FIRST:

@@ -16,6 +16,7 @@
 #include <cstring>
 
 #include "nlpr_internal.h"
+#include "pupdate.h"
 
 namespace nlpr {
 namespace {
@@ -717,276 +718,12 @@ conv_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, in
 }
 
 // ---------------------------------------------------------------------------- pupdate
-// Work item = 256 pixels.  A pixel has NC threads (1, or 4 when the launch covers few pixels in
-// all, so that it still fills the GPU), each owning a contiguous share of the bands; with 4 a
-// workgroup takes a quarter of the item's pixels, one wave per share, so that the exchange of
-// the shares holds up four waves instead of sixteen.
-// With E = I:
-//   P1 = (rho BX + Y_l - rho Lambda1) / (1 + rho)  on sampled pixels (S^T S = 1)
-//   P1 = BX - Lambda1                              elsewhere            (eq. (Qh_update))
-//   P2 = (X - Lambda2 + lambda1/rho Y_h R^T) F,  F = (I + lambda1/rho R R^T)^{-1}
-//                                                                       (eq. (Qm_update))
-// P2 is evaluated as  P2 = A0 + (Y_h - A0 R) G R^T  with A0 = X - Lambda2 and
-// G = (rho/lambda1 I + R^T R)^{-1}: Woodbury gives F = I - R G R^T and the push-through
-// identity R^T F = (I + lambda1/rho R^T R)^{-1} R^T turns lambda1/rho Y_h R^T F into
-// Y_h G R^T.  The rearrangement is exact and keeps every FP32 term O(|X|) instead of
-// O(lambda1/rho |Y_h|), which avoids a large cancellation.  The contraction A0 R over
-// bands is summed per band share and the parts are added in share order (through LDS when a
-// pixel has several threads).
-//   Lambda1 -= BX - P1,  Lambda2 -= X - P2;  W1 = P1 + Lambda1,  W2 = P2 + Lambda2
-// Off the sampled pixels P1 = BX - Lambda1 gives Lambda1 = Lambda1 - (BX - P1) = 0 and W1 = BX,
-// exactly, from Lambda1 = 0 at the start: so when B X arrives in W1 (bx_s == w1_s) only the
-// sampled pixels, one in d^2, have a P1 to update.  Per pixel and band that leaves 16 bytes (X
-// and Lambda2 read, Lambda2 and W2 written) of 32: a 12-scene batch, whose P-update runs beside
-// the sweep, 16.6 -> 15.7 ms per 10-iteration solve; 256 x 256 x 31, where the launch is bound by
-// latency, 15.1 -> 14.7 us.
-// Band shares of the contraction A0 R in the P-update: fixed, so that the sum is the same
-// whichever number of threads a pixel has.
-constexpr int kPuShares = 4;
-
-// rp += sum over bands [c0, c1) of (X - Lambda2)_c R_c, one fused multiply-add per term.
-template <int LHM>
-__device__ __forceinline__ void pupdate_share(const gfloat* __restrict__ X,
-                                              const gfloat* __restrict__ L2,
-                                              const gfloat* __restrict__ R, float (&rp)[LHM],
-                                              size_t plane, int Lh, int c0, int c1, int j) {
-  for (int c = c0; c < c1; ++c) {
-    const float a0 = X[c * plane + j] - L2[c * plane + j];
-#pragma unroll
-    for (int h = 0; h < LHM; ++h)
-      if (h < Lh) rp[h] = __builtin_fmaf(a0, R[c * Lh + h], rp[h]);
-  }
-}
-
-// Bands [c0, c1) of one pixel: P2, Lambda2, W2 and, where p1, P1, Lambda1 and W1.  Lambda is
-// read through L1, L2 and written through L1o, L2o, which may be the same buffers, and BX may
-// be W1 (no restrict on those six); BXo, if not null, also takes B X where p1.  R arrives as a restrict parameter so that the compiler may read
-// it with scalar loads across the stores (restrict on local pointer variables is not used
-// for that).
-template <int LHM>
-__device__ __forceinline__ void pupdate_write(
-    const gfloat* __restrict__ X, const gfloat* BX, const gfloat* __restrict__ Yl,
-    const gfloat* L1, const gfloat* L2, gfloat* L1o, gfloat* L2o, gfloat* W1,
-    gfloat* __restrict__ W2, gfloat* BXo, const gfloat* __restrict__ R, const float (&u)[LHM],
-    size_t plane, size_t lplane, size_t lj, bool sampled, bool p1, int Lh, float rho,
-    float inv_1prho, int c0, int c1, int j) {
-  for (int c = c0; c < c1; ++c) {
-    const size_t o = c * plane + j;
-    float corr = 0.f;
-#pragma unroll
-    for (int h = 0; h < LHM; ++h)
-      if (h < Lh) corr += u[h] * R[c * Lh + h];
-    const float x = X[o], l2 = L2[o];
-    const float p2 = (x - l2) + corr;
-    const float l2n = l2 - (x - p2);
-    L2o[o] = l2n;
-    W2[o] = p2 + l2n;
-    if (!p1) continue;
-    const float bx = BX[o], l1 = L1[o];
-    const float p1v = sampled ? (rho * bx + Yl[c * lplane + lj] - rho * l1) * inv_1prho : bx - l1;
-    const float l1n = l1 - (bx - p1v);
-    L1o[o] = l1n;
-    W1[o] = p1v + l1n;
-    if (BXo) BXo[o] = bx;
-  }
-}
-
-// With at most kPuKeep bands per thread, X and Lambda2 are read once: the contraction pass
-// keeps them in registers for the write pass (32 bytes per pixel and band instead of 40).
-// Same operations in the same order as the two functions above.
-constexpr int kPuKeep = 16;
-
-// All loads of the thread's bands up front (X, Lambda2, and for P1 BX and Lambda1), so that
-// their latencies overlap: the contraction pass then only waits for X and Lambda2.
-template <int LHM>
-__device__ __forceinline__ void pupdate_load_keep(const gfloat* __restrict__ X,
-                                                  const gfloat* __restrict__ L2,
-                                                  const gfloat* BX, const gfloat* L1,
-                                                  const gfloat* __restrict__ Yl, bool p1,
-                                                  bool sampled, size_t plane, size_t lplane,
-                                                  size_t lj, int c0, int c1, int j,
-                                                  float (&xs)[kPuKeep], float (&l2s)[kPuKeep],
-                                                  float (&bxs)[kPuKeep], float (&l1s)[kPuKeep],
-                                                  float (&yls)[kPuKeep]) {
-#pragma unroll
-  for (int i = 0; i < kPuKeep; ++i) {
-    const int c = c0 + i;
-    if (c < c1) {
-      xs[i] = X[c * plane + j];
-      l2s[i] = L2[c * plane + j];
-    }
-  }
-  if (!p1) return;
-#pragma unroll
-  for (int i = 0; i < kPuKeep; ++i) {
-    const int c = c0 + i;
-    if (c < c1) {
-      bxs[i] = BX[c * plane + j];
-      l1s[i] = L1[c * plane + j];
-      if (sampled) yls[i] = Yl[c * lplane + lj];
-    }
-  }
-}
-
-// rp += sum over bands [cs, ce) of (X - Lambda2)_c R_c, from the kept values (band c at
-// register c - c0)
-template <int LHM>
-__device__ __forceinline__ void pupdate_share_kept(const float (&xs)[kPuKeep],
-                                                   const float (&l2s)[kPuKeep],
-                                                   const gfloat* __restrict__ R,
-                                                   float (&rp)[LHM], int Lh, int c0, int cs,
-                                                   int ce) {
-#pragma unroll
-  for (int i = 0; i < kPuKeep; ++i) {
-    const int c = c0 + i;
-    if (c >= cs && c < ce) {
-      const float a0 = xs[i] - l2s[i];
-#pragma unroll
-      for (int h = 0; h < LHM; ++h)
-        if (h < Lh) rp[h] = __builtin_fmaf(a0, R[c * Lh + h], rp[h]);
-    }
-  }
-}
-
-template <int LHM>
-__device__ __forceinline__ void pupdate_write_kept(
-    const float (&xs)[kPuKeep], const float (&l2s)[kPuKeep], const float (&bxs)[kPuKeep],
-    const float (&l1s)[kPuKeep], const float (&yls)[kPuKeep], gfloat* L1o, gfloat* L2o,
-    gfloat* __restrict__ W1, gfloat* __restrict__ W2, gfloat* BXo, const gfloat* __restrict__ R,
-    const float (&u)[LHM], size_t plane, bool sampled, bool p1, int Lh, float rho,
-    float inv_1prho, int c0, int c1, int j) {
-#pragma unroll
-  for (int i = 0; i < kPuKeep; ++i) {
-    const int c = c0 + i;
-    if (c >= c1) continue;
-    const size_t o = c * plane + j;
-    float corr = 0.f;
-#pragma unroll
-    for (int h = 0; h < LHM; ++h)
-      if (h < Lh) corr += u[h] * R[c * Lh + h];
-    const float x = xs[i], l2 = l2s[i];
-    const float p2 = (x - l2) + corr;
-    const float l2n = l2 - (x - p2);
-    L2o[o] = l2n;
-    W2[o] = p2 + l2n;
-    if (!p1) continue;
-    const float bx = bxs[i], l1 = l1s[i];
-    const float p1v = sampled ? (rho * bx + yls[i] - rho * l1) * inv_1prho : bx - l1;
-    const float l1n = l1 - (bx - p1v);
-    L1o[o] = l1n;
-    W1[o] = p1v + l1n;
-    if (BXo) BXo[o] = bx;
-  }
-}
-
 template <int LHM, int PU_NC, bool KEEP>
 __global__ void __launch_bounds__(256)
-pupdate_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
-               int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1_s, int w2_s, int l1o_s,
-               int l2o_s, int bxo_s) {
-  constexpr int PX = 256 / PU_NC;          // pixels of the workgroup
-  __shared__ float part[PU_NC > 1 ? PU_NC : 1][PU_NC > 1 ? LHM : 1][PU_NC > 1 ? PX : 1];
+pupdate_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, PuSlots sl) {
+  __shared__ float part[pupdate_lds_floats(LHM, PU_NC)];
   const int2 it = work_item(items, blockIdx.x / PU_NC);
-  const SceneDesc& S = sd[it.x];
-  const int p = S.p, q = S.q, L = S.L, Lh = S.Lh, d = S.d;
-  // the band share is uniform over a wave; readfirstlane lets the band loops index R and G
-  // with scalar loads
-  const int pix = threadIdx.x & (PX - 1);
-  const int ch = PU_NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PX);
-  const int j = it.y * 256 + (blockIdx.x % PU_NC) * PX + pix;
-  const size_t plane = (size_t)p * q;
-  const bool act = j < (int)plane;
-  const int c0 = (L * ch) / PU_NC, c1 = (L * (ch + 1)) / PU_NC;   // this thread's bands
-  const gfloat* __restrict__ X = gslot<const gfloat>(S, x_s);
-  const gfloat* L2 = gslot<const gfloat>(S, l2_s);
-  const gfloat* __restrict__ R = as_global(S.R);
-  const gfloat* __restrict__ G = as_global(S.G);
-  const gfloat* __restrict__ Yh = gslot<const gfloat>(S, yh_s);
-  // res = Y_h - A0 R.  The bands form kPuShares contiguous shares; each share's part of A0 R
-  // is summed on its own and the parts are added in share order, so the result does not
-  // depend on how many threads a pixel has.
-  float res[LHM];
-  // KEEP: every scene of the launch has at most kPuKeep bands per thread
-  const int i1 = j / q, i2 = j - i1 * q;
-  const bool sampled = (i1 % d == 0) && (i2 % d == 0);
-  // no P1 with the fused-S splitting; with a basis p1_subspace_kernel updates the sampled
-  // pixels; and with W1 in place of B X the others hold their W1 (see launch_pupdate)
-  const bool p1 = !S.fused && (sampled ? !S.subspace : bx_s != w1_s);
-  const size_t lplane = (size_t)(p / d) * (q / d), lj = (size_t)(i1 / d) * (q / d) + i2 / d;
-  float xs[KEEP ? kPuKeep : 1], l2s[KEEP ? kPuKeep : 1], bxs[KEEP ? kPuKeep : 1],
-      l1s[KEEP ? kPuKeep : 1], yls[KEEP ? kPuKeep : 1], yh[LHM];
-  if constexpr (KEEP)
-    if (act)
-    pupdate_load_keep<LHM>(X, L2, gslot<const gfloat>(S, bx_s), gslot<const gfloat>(S, l1_s),
-                           gslot<const gfloat>(S, yl_s), p1, sampled, plane, lplane, lj, c0, c1,
-                           j, xs, l2s, bxs, l1s, yls);
-  if (act) {
-#pragma unroll
-    for (int h = 0; h < LHM; ++h) yh[h] = (h < Lh) ? Yh[h * plane + j] : 0.f;
-  }
-  if constexpr (PU_NC == 1) {
-    // one thread per pixel: the parts are added in registers, and no barrier sits between
-    // the two band loops (with one the memory-bound loops of different waves do not overlap)
-    if (!act) return;
-    float a[LHM];
-#pragma unroll
-    for (int h = 0; h < LHM; ++h) a[h] = 0.f;
-    for (int k = 0; k < kPuShares; ++k) {
-      float rp[LHM];
-#pragma unroll
-      for (int h = 0; h < LHM; ++h) rp[h] = 0.f;
-      if constexpr (KEEP)
-        pupdate_share_kept<LHM>(xs, l2s, R, rp, Lh, c0, (L * k) / kPuShares,
-                                (L * (k + 1)) / kPuShares);
-      else
-        pupdate_share<LHM>(X, L2, R, rp, plane, Lh, (L * k) / kPuShares,
-                           (L * (k + 1)) / kPuShares, j);
-#pragma unroll
-      for (int h = 0; h < LHM; ++h) a[h] += rp[h];
-    }
-#pragma unroll
-    for (int h = 0; h < LHM; ++h) res[h] = (h < Lh) ? yh[h] - a[h] : 0.f;
-  } else {
-    static_assert(PU_NC == kPuShares, "one share per thread");
-    float rp[LHM];
-#pragma unroll
-    for (int h = 0; h < LHM; ++h) rp[h] = 0.f;
-    if (act) {
-      if constexpr (KEEP) pupdate_share_kept<LHM>(xs, l2s, R, rp, Lh, c0, c0, c1);
-      else pupdate_share<LHM>(X, L2, R, rp, plane, Lh, c0, c1, j);
-    }
-#pragma unroll
-    for (int h = 0; h < LHM; ++h) part[ch][h][pix] = rp[h];
-    __syncthreads();
-    if (!act) return;
-#pragma unroll
-    for (int h = 0; h < LHM; ++h) {
-      float a = 0.f;
-#pragma unroll
-      for (int k = 0; k < PU_NC; ++k) a += part[k][h][pix];
-      res[h] = (h < Lh) ? yh[h] - a : 0.f;
-    }
-  }
-  float u[LHM];                           // u = res G
-#pragma unroll
-  for (int h2 = 0; h2 < LHM; ++h2) {
-    float sum = 0.f;
-#pragma unroll
-    for (int h = 0; h < LHM; ++h)
-      if (h < Lh && h2 < Lh) sum += res[h] * G[h * Lh + h2];
-    u[h2] = sum;
-  }
-  if constexpr (KEEP)
-    pupdate_write_kept<LHM>(xs, l2s, bxs, l1s, yls, gslot<gfloat>(S, l1o_s),
-                            gslot<gfloat>(S, l2o_s), gslot<gfloat>(S, w1_s),
-                            gslot<gfloat>(S, w2_s), gslot<gfloat>(S, bxo_s), R, u, plane,
-                            sampled, p1, Lh, S.rho, S.inv_1prho, c0, c1, j);
-  else
-    pupdate_write<LHM>(X, gslot<const gfloat>(S, bx_s), gslot<const gfloat>(S, yl_s),
-                       gslot<const gfloat>(S, l1_s), L2, gslot<gfloat>(S, l1o_s),
-                       gslot<gfloat>(S, l2o_s), gslot<gfloat>(S, w1_s), gslot<gfloat>(S, w2_s),
-                       gslot<gfloat>(S, bxo_s), R, u, plane, lplane, lj, sampled, p1, Lh, S.rho,
-                       S.inv_1prho, c0, c1, j);
+  pupdate_body<LHM, PU_NC, KEEP>(sd[it.x], it.y, blockIdx.x % PU_NC, sl, part);
 }
 
 template <typename Kern, typename... Args>
@@ -1220,34 +957,28 @@ int launch_conv(const Batch& B, int in, int out, bool transpose, int add1, int a
 }
 
 template <int LHM, int NC>
-void launch_pu(const Batch& B, const Group& g, int x, int bx, int yl, int yh, int l1, int l2,
-               int w1, int w2, int l1o, int l2o, int bxo, hipStream_t s) {
+void launch_pu(const Batch& B, const Group& g, const PuSlots& sl, hipStream_t s) {
   int maxL = 0;
   for (const auto& P : B.scenes) maxL = std::max(maxL, P->Lx);
-  if (maxL <= kPuKeep * NC)
-    hipLaunchKernelGGL((pupdate_kernel<LHM, NC, true>), dim3(g.nitems * NC), dim3(256), 0, s,
-                       B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
-  else
-    hipLaunchKernelGGL((pupdate_kernel<LHM, NC, false>), dim3(g.nitems * NC), dim3(256), 0, s,
-                       B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo);
+  auto kern = maxL <= kPuKeep * NC ? pupdate_kernel<LHM, NC, true> : pupdate_kernel<LHM, NC, false>;
+  hipLaunchKernelGGL(kern, dim3(g.nitems * NC), dim3(256), 0, s, B.d_desc, items_of(B, g), sl);
 }
 
-int launch_pupdate(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1, int w2,
-                   int l1o, int l2o, int bxo, hipStream_t s) {
+int launch_pupdate(const Batch& B, const PuSlots& sl, hipStream_t s) {
   // one launch per guide-band class (key0 = 1, 4 or 16 register slots) and threads per
   // pixel (key1 = 1 or 4)
   for (const Group& g : B.groups[KD_PIXEL]) {
     if (!g.nitems) continue;
     const bool split = g.key1 == 4;
     if (g.key0 == 1) {
-      if (split) launch_pu<1, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
-      else launch_pu<1, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
+      if (split) launch_pu<1, 4>(B, g, sl, s);
+      else launch_pu<1, 1>(B, g, sl, s);
     } else if (g.key0 == 4) {
-      if (split) launch_pu<4, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
-      else launch_pu<4, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
+      if (split) launch_pu<4, 4>(B, g, sl, s);
+      else launch_pu<4, 1>(B, g, sl, s);
     } else {
-      if (split) launch_pu<kMaxLh, 4>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
-      else launch_pu<kMaxLh, 1>(B, g, x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo, s);
+      if (split) launch_pu<kMaxLh, 4>(B, g, sl, s);
+      else launch_pu<kMaxLh, 1>(B, g, sl, s);
     }
     NLPR_LAUNCH_CHECK("pupdate_kernel");
   }

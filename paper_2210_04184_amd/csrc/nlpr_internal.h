@@ -106,6 +106,13 @@ constexpr int kSweepThreads = 256;   // workgroup size of the sweep
 // more than the overlap gains (256 x 256 x 31: 2.77 -> 2.90 ms per solve; 512 x 512 x 128:
 // 3.03 -> 2.98 s).
 constexpr size_t kForkPixelBands = (size_t)1 << 22;
+// A single scene above it that can have both in one launch (sweep_pu) does without the second
+// stream below this many pixels, unless it has a basis, whose P1 is a launch of its own.  Per
+// iteration, second stream and one launch: 512 x 512 x 24 5x5/5x5 1010 and 910 us, 512 x 512 x 31 3x3/3x3
+// 345 and 323, 512 x 512 x 16 5x5/11x11 2705 and 2595, 768 x 768 x 8 5x5/5x5 940 and 908; but
+// 1024 x 1024 x 4 3x3/3x3 291 and 303, 1024 x 1024 x 8 3x3/5x5 833 and 838, and 512 x 512 with a
+// 20-band basis 2491 and 2497 (there the second stream hides the blur too).
+constexpr size_t kForkPixels = (size_t)1 << 20;
 // Cache policies of the sweep's dual state: nothing, the packed values, or all of it bypass
 // the caches (non-temporal).
 enum SweepPolicy { kSweepCached = 0, kSweepCodesCached = 1, kSweepStream = 2 };
@@ -255,6 +262,8 @@ __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; 
 typedef __attribute__((address_space(1))) float gfloat;
 typedef __attribute__((address_space(1))) uint8_t gu8;
 typedef __attribute__((address_space(1))) double gdouble;
+// small tables read at wave-uniform addresses: scalar loads whatever stores surround them
+typedef __attribute__((address_space(4))) const float cfloat;
 typedef float v2f_t __attribute__((ext_vector_type(2)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef int v2i_t __attribute__((ext_vector_type(2)));
@@ -268,6 +277,7 @@ constexpr int kCacheNT = 2;
 // no stride, no swizzle; offsets are bytes from the base
 constexpr int kRawBufferFlags = 0x00020000;
 __device__ __forceinline__ const gfloat* as_global(const float* p) { return (const gfloat*)p; }
+__device__ __forceinline__ cfloat* as_constant(const float* p) { return (cfloat*)p; }
 __device__ __forceinline__ gfloat* as_global(float* p) { return (gfloat*)p; }
 template <typename G>
 __device__ __forceinline__ G* gslot(const SceneDesc& S, int k) {
@@ -334,8 +344,11 @@ int launch_conv(const Batch& B, int in, int out, bool transpose, int add1, int a
 // update in place).  bx == w1: B X lies in W1 and only the sampled pixels' P1, Lambda1 and W1
 // are updated, the others being P1 + Lambda1 = B X with Lambda1 = 0 already.  bxo >= 0: the slot
 // that also takes B X where P1 is updated.
-int launch_pupdate(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1, int w2,
-                   int l1o, int l2o, int bxo, hipStream_t s);
+// buffer slots of the P-update (bxo: -1, or where B X also goes)
+struct PuSlots {
+  int x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo;
+};
+int launch_pupdate(const Batch& B, const PuSlots& sl, hipStream_t s);
 // Re-point buffer slots of the descriptor of scene 0 on the stream: kernels enqueued after it
 // see the new buffers.  The reverse-mode passes move through their checkpoints this way.
 struct SlotSet {
@@ -401,6 +414,10 @@ int launch_xsolve(const Batch& B, int c, int x, int f, int add, hipStream_t s);
 // number of open items written (float4s stored) to *count.
 int launch_sweep(const Batch& B, int x, int mu, int sigma, int creg, int halo, bool first,
                  hipStream_t s, uint8_t* codes = nullptr, unsigned long long* count = nullptr);
+// the P-update and a sweep but the first in one launch, for batches where sweep_pu
+bool sweep_pu(const Batch& B);
+int launch_sweep_pu(const Batch& B, const PuSlots& sl, int x, int mu, int sigma, int creg,
+                    int halo, hipStream_t s, uint8_t* codes);
 // Dense Sigma' of bands [c0, c0 + nb) of scene 0: [nb][Npairs][|P|][p][q]
 int launch_sigma_expand(const Batch& B, const float* sig, const uint8_t* codes, const float* mu,
                         int c0, int nb, float* out, hipStream_t s);

@@ -33,6 +33,7 @@
 // plane and its halo rows as above, part j > 0 its own plane (slot B_CSPLIT) and halo rows;
 // the assembly adds the parts in a fixed order, so results stay bit-for-bit repeatable.
 #include "nlpr_internal.h"
+#include "pupdate.h"
 
 namespace nlpr {
 namespace {
@@ -91,11 +92,11 @@ __device__ __forceinline__ float clampf(float v, float m) { return fminf(fmaxf(v
 // kCountSlots counters there (kCountStride apart); their sum is the launch's count.
 // POLICY: which part of the dual state passes the caches by (sweep_policy).
 template <int K, int ITEMS, int NT, bool FIRST, bool CODES, int POLICY>
-__global__ void __launch_bounds__(NT)
-sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s, int mu_s,
-             int sig_s, int code_s, int creg_s, int halo_s, uint8_t* codes,
-             unsigned long long* count) {
-  const int2 it_ = items[blockIdx.x];
+__device__ __forceinline__ void
+sweep_body(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int block, int x_s,
+           int mu_s, int sig_s, int code_s, int creg_s, int halo_s, uint8_t* codes,
+           unsigned long long* count) {
+  const int2 it_ = items[block];
   const SceneDesc& S = sd[it_.x];
   const int p = S.p, q = S.q, L = S.L, npairs = S.npairs, R = S.rows, ntiles = S.ntiles,
             H = S.halo, split = S.psplit;
@@ -558,7 +559,7 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
   if (count && (threadIdx.x & 63) == 0) {
     // spread over kCountSlots counters a cache line apart: waves that end together on one
     // address would queue behind each other at the L2
-    const unsigned slot = (blockIdx.x * (NT / 64) + threadIdx.x / 64) % kCountSlots;
+    const unsigned slot = (block * (NT / 64) + threadIdx.x / 64) % kCountSlots;
     atomicAdd(count + (size_t)slot * kCountStride, (unsigned long long)open_written);
   }
   __syncthreads();
@@ -579,6 +580,39 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
       stg4(hb + 4 * e, make_float4(2.f * v.x, 2.f * v.y, 2.f * v.z, 2.f * v.w));
     }
   }
+}
+
+template <int K, int ITEMS, int NT, bool FIRST, bool CODES, int POLICY>
+__global__ void __launch_bounds__(NT)
+sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s, int mu_s,
+             int sig_s, int code_s, int creg_s, int halo_s, uint8_t* codes,
+             unsigned long long* count) {
+  sweep_body<K, ITEMS, NT, FIRST, CODES, POLICY>(sd, items, blockIdx.x, x_s, mu_s, sig_s, code_s,
+                                                 creg_s, halo_s, codes, count);
+}
+
+// The sweep (the first nsw workgroups) and the P-update (the rest), which read X and write
+// disjoint buffers.  A P-update of its own is bound by latency up to 256 x 256 (13.9 us for 40 MB at
+// 31 bands) and costs a launch; here its workgroups fill the end of the sweep, whose last
+// workgroups leave CUs idle.  It stays within the sweep's registers (K <= 3), so the sweep's
+// occupancy is the same.  Per iteration of a solve: 64 x 64 x 8 (graph) 36.2 -> 32.2 us, 128 x 128 x 31
+// 65 -> 58, 192 x 256 x 31 fused-S 88 -> 80, 256 x 256 x 31 103 -> 96; with the P-update's
+// workgroups first, 88 -> 90 and 103 -> 102.
+template <int K, bool CODES, int POLICY>
+__global__ void __launch_bounds__(256)
+sweep_pu_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
+                int mu_s, int sig_s, int code_s, int creg_s, int halo_s, uint8_t* codes,
+                PuSlots sl, int nsw, int lhm) {
+  const int b = (int)blockIdx.x - nsw;
+  if (b >= 0) {
+    extern __shared__ float4 lds4[];
+    float* part = reinterpret_cast<float*>(lds4);
+    if (lhm == 1) pupdate_body<1, 4, true>(sd[0], b / 4, b % 4, sl, part);
+    else pupdate_body<4, 4, true>(sd[0], b / 4, b % 4, sl, part);
+    return;
+  }
+  sweep_body<K, 1, 256, false, CODES, POLICY>(sd, items, blockIdx.x, x_s, mu_s, sig_s, code_s,
+                                              creg_s, halo_s, codes, nullptr);
 }
 
 // ---- sweep kernel end
@@ -619,6 +653,10 @@ int set_lds_limit() {
   if constexpr (ITEMS == 1)
     if ((rc = lds_limit(sweep_kernel<K, ITEMS, NT, true, true, POLICY>)) ||
         (rc = lds_limit(sweep_kernel<K, ITEMS, NT, false, true, POLICY>)))
+      return rc;
+  if constexpr (K <= 3 && ITEMS == 1)
+    if ((rc = lds_limit(sweep_pu_kernel<K, false, POLICY>)) ||
+        (rc = lds_limit(sweep_pu_kernel<K, true, POLICY>)))
       return rc;
   return NLPR_OK;
 }
@@ -672,7 +710,54 @@ int launch_items(const Batch& B, const Group& g, int x, int mu, int sig, int cre
   }
 }
 
+template <int K, bool CODES, int POLICY>
+int launch_kpu(const Batch& B, const Group& g, const Group& gp, const PuSlots& sl, int x, int mu,
+               int sig, int creg, int halo, uint8_t* codes, hipStream_t s) {
+  auto kern = sweep_pu_kernel<K, CODES, POLICY>;
+  const size_t lds = std::max(g.lds, sizeof(float) * pupdate_lds_floats(4, 4));
+  hipLaunchKernelGGL(kern, dim3(g.nitems + 4 * gp.nitems), dim3(256), lds, s, B.d_desc, g.d_items, x, mu,
+                     sig, (int)B_SCODE, creg, halo, codes, sl, g.nitems, gp.key0);
+  NLPR_LAUNCH_CHECK("sweep_pu_kernel");
+  return NLPR_OK;
+}
+
+template <int K>
+int launch_pu_k(const Batch& B, const Group& g, const Group& gp, const PuSlots& sl, int x, int mu,
+                int sig, int creg, int halo, uint8_t* codes, hipStream_t s) {
+  switch (g.policy) {
+    case kSweepCached:
+      return codes ? launch_kpu<K, true, kSweepCached>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s)
+                   : launch_kpu<K, false, kSweepCached>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+    case kSweepCodesCached:
+      return codes ? launch_kpu<K, true, kSweepCodesCached>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s)
+                   : launch_kpu<K, false, kSweepCodesCached>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+    default:
+      return codes ? launch_kpu<K, true, kSweepStream>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s)
+                   : launch_kpu<K, false, kSweepStream>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+  }
+}
+
 }  // namespace
+
+// One scene without a second stream (kForkPixelBands), tiles of one item per thread, and bands
+// that four threads per pixel can hold; timing keeps the stages apart.
+bool sweep_pu(const Batch& B) {
+  if (B.scenes.size() != 1 || B.side || B.timing) return false;
+  const auto &gs = B.groups[KD_SWEEP], &gp = B.groups[KD_PIXEL];
+  return gs.size() == 1 && gs[0].nitems && gs[0].key1 == 1 && gs[0].key0 <= 3 &&
+         gp.size() == 1 && gp[0].key0 <= 4 && B.scenes[0]->Lx <= 4 * kPuKeep;
+}
+
+int launch_sweep_pu(const Batch& B, const PuSlots& sl, int x, int mu, int sig, int creg, int halo,
+                    hipStream_t s, uint8_t* codes) {
+  const Group &g = B.groups[KD_SWEEP][0], &gp = B.groups[KD_PIXEL][0];
+  switch (g.key0) {
+    case 0: return launch_pu_k<0>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+    case 1: return launch_pu_k<1>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+    case 2: return launch_pu_k<2>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+    default: return launch_pu_k<3>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
+  }
+}
 
 SweepShape choose_sweep_shape(int p, int q, int K, int halo) {
   SweepShape sh{};

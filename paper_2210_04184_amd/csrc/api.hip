@@ -554,7 +554,7 @@ int batch_build(Batch& B) {
   // work-item tables, descriptors, the finite check's flag and the open-item counters: one
   // allocation
   const size_t o_desc = align256(std::max<size_t>(B.tables.size(), 1) * sizeof(int2));
-  const size_t o_flag = align256(o_desc + n * sizeof(SceneDesc));
+  const size_t o_flag = align256(o_desc + (n > 1 ? n : 1 + kDescRing) * sizeof(SceneDesc));
   const size_t o_counts = o_flag + 256;
   const size_t counts = B.timing ? (size_t)std::max(B.iters, 1) * kCountSlots * kCountStride *
                                        sizeof(unsigned long long)
@@ -935,9 +935,35 @@ uint8_t* ck_codes(void* ck, const GradLayout& G, int T, int t) {
          (size_t)(t - 1) * G.code_al;
 }
 
+// The launches of a reverse-mode pass use descriptor 1 + i of B while this is at i.
+struct DescRing {
+  Batch& B;
+  SceneDesc* const first;
+  SlotTable tab;
+  explicit DescRing(Batch& b) : B(b), first(b.d_desc) {}
+  ~DescRing() { B.d_desc = first; }
+  // Go to entry i of a pass of `total` entries.  Every kDescRing entries the next ones are
+  // filled in: fill(entry, pointers) sets the pointers, which start as the scene's own.
+  template <typename Fill>
+  int at(int i, int total, const SceneDesc& d, hipStream_t s, Fill fill) {
+    if (i % kDescRing == 0) {
+      tab.count = std::min(kDescRing, total - i);
+      for (int e = 0; e < tab.count; ++e) {
+        for (int k = 0; k < tab.n; ++k) tab.ptr[e][k] = d.buf[tab.slot[k]];
+        fill(i + e, tab.ptr[e]);
+      }
+      B.d_desc = first;
+      const int rc = launch_desc_ring(B, tab, s);
+      if (rc) return rc;
+    }
+    B.d_desc = first + 1 + i % kDescRing;
+    return NLPR_OK;
+  }
+};
+
 // Forward solve that keeps the checkpoints.  Z = X^T equals nlpr_solve's output bit for bit;
 // the last iteration stops after its X-update, the only part of it that reaches Z.  Nothing
-// is copied: before each iteration the descriptor's slots are re-pointed so that the X-update
+// is copied: each iteration has its own descriptor, whose slots are such that the X-update
 // writes X^t into checkpoint t, and the P-update writes B X^t there, reads the Lambda of
 // checkpoint t and writes the new Lambda into checkpoint t+1 (the workspace after the last).
 // The sweep updates Sigma' in place in the workspace, as in the solve, and writes the branch
@@ -958,40 +984,37 @@ int grad_forward(Batch& B, const float* Yl, const float* Yh, float* Z, void* ws,
     return fail(NLPR_ERR_WORKSPACE_TOO_SMALL, "workspace or checkpoint buffer too small");
   char* base = static_cast<char*>(ws);
   std::vector<SceneDesc> descs{solve_desc(P, base, Yl, Yh, Z)};
-  DeviceGuard dg(B.device);
-  if ((rc = upload_desc(B, descs, s))) return rc;
   const int T = B.iters;
   const bool reg = P.npairs > 0;
-  B.desc_valid = false;          // the slots below change the device copy
   auto plane = [&](int t, int k) -> void* { return ck_plane(ck, G, t, k); };
   void* wl1 = base + P.off[B_L1];
   void* wl2 = base + P.off[B_L2];
+  if (T > 1) {                   // the start's Lambda (zeros) goes into checkpoint 1
+    descs[0].buf[B_L1] = plane(1, 2);
+    descs[0].buf[B_L2] = plane(1, 3);
+  }
+  DeviceGuard dg(B.device);
+  if ((rc = upload_desc(B, descs, s))) return rc;
   if ((rc = launch_weights(B, B_YH, B_MU, s))) return rc;
   // Lambda1 is zero off the sampled pixels, which alone the checkpoints carry: the workspace's
   // plane, which takes it after the last P-update, gets its zeros here
-  if ((rc = launch_fill(B, B_L1, s))) return rc;
-  if (T > 1) {                   // the start's Lambda (zeros) goes into checkpoint 1
-    SlotSet st;
-    st.add(B_L1, plane(1, 2));
-    st.add(B_L2, plane(1, 3));
-    if ((rc = launch_set_slots(B, st, s))) return rc;
-  }
+  if ((rc = launch_fill(B, B_L1O, s))) return rc;
   if ((rc = launch_init(B, B_YL, B_YLP, B_Z, B_L1, B_L2, B_W2, s))) return rc;
   if ((rc = launch_conv(B, B_Z, B_W1, false, -1, -1, -1, 0, s))) return rc;
   if ((rc = launch_conv(B, B_W1, B_C, true, B_W2, -1, -1, 0, s))) return rc;
+  DescRing ring(B);
+  ring.tab.n = 6;
+  const int slots[6] = {B_Z, B_BX, B_L1, B_L2, B_L1O, B_L2O};
+  std::copy(slots, slots + 6, ring.tab.slot);
   for (int t = 1; t <= T; ++t) {
-    if (T > 1) {
-      SlotSet st;
-      st.add(B_Z, t < T ? plane(t, 0) : static_cast<void*>(Z));
-      if (t < T) {
-        st.add(B_BX, plane(t, 1));
-        st.add(B_L1, plane(t, 2));
-        st.add(B_L2, plane(t, 3));
-        st.add(B_L1O, t + 1 < T ? plane(t + 1, 2) : wl1);
-        st.add(B_L2O, t + 1 < T ? plane(t + 1, 3) : wl2);
-      }
-      if ((rc = launch_set_slots(B, st, s))) return rc;
-    }
+    rc = ring.at(t - 1, T, descs[0], s, [&](int i, void** ptr) {
+      const int u = i + 1;         // iteration; the last has Z and no P-update
+      if (u == T) return;
+      for (int k = 0; k < 4; ++k) ptr[k] = plane(u, k);
+      ptr[4] = u + 1 < T ? plane(u + 1, 2) : wl1;
+      ptr[5] = u + 1 < T ? plane(u + 1, 3) : wl2;
+    });
+    if (rc) return rc;
     if ((rc = launch_xsolve(B, B_C, B_Z, B_F, -1, s))) return rc;
     if (t == T) break;
     if ((rc = launch_conv(B, B_Z, B_W1, false, -1, -1, -1, 0, s))) return rc;
@@ -1047,7 +1070,6 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
   std::vector<SceneDesc> descs{d};
   DeviceGuard dg(B.device);
   if ((rc = upload_desc(B, descs, s))) return rc;
-  B.desc_valid = false;          // the checkpoint slots below change the device copy
   const bool reg = P.npairs > 0;
   const int p = P.prm.p, q = P.prm.q, d_ = P.prm.d;
   const size_t pl = (size_t)P.Lx * p * q * sizeof(float);
@@ -1061,13 +1083,18 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
   if ((rc = launch_weights(B, B_YH, B_MU, s))) return rc;
   // Z = X^T = solve(C^{T-1})
   if ((rc = launch_xsolve(B, B_GZ, B_GC, B_F, -1, s))) return rc;
+  DescRing ring(B);
+  ring.tab.n = 6;
+  const int slots[6] = {B_Z, B_BX, B_L1, B_L2, B_GC, B_GCP};
+  std::copy(slots, slots + 6, ring.tab.slot);
+  auto fill = [&](int i, void** ptr) {
+    const int u = T - 1 - i;       // X^u, B X^u and the Lambda entering iteration u; C'
+    for (int k = 0; k < 4 && u > 0; ++k) ptr[k] = ck_plane(ck, G, u, k);
+    ptr[4] = cbuf[u & 1];
+    ptr[5] = cbuf[(u + 1) & 1];
+  };
   for (int t = T - 1; t >= 1; --t) {
-    SlotSet st;                  // X^t, B X^t and the Lambda entering iteration t; C'
-    for (int k = 0; k < 4; ++k) st.add(k == 0 ? B_Z : k == 1 ? B_BX : k == 2 ? B_L1 : B_L2,
-                                       ck_plane(ck, G, t, k));
-    st.add(B_GC, cbuf[t & 1]);
-    st.add(B_GCP, cbuf[(t + 1) & 1]);
-    if ((rc = launch_set_slots(B, st, s))) return rc;
+    if ((rc = ring.at(T - 1 - t, T, d, s, fill))) return rc;
     if ((rc = launch_conv(B, B_GC, B_GW1, false, -1, -1, -1, 0, s))) return rc;   // W1' = B C'
     if (reg && (rc = launch_sweep_bwd(B, B_GC, ck_codes(ck, G, T, t), B_GSIG, B_GXR, B_GHALO,
                                       B_GMUP, t + 1 < T ? ck_codes(ck, G, T, t + 1) : nullptr,
@@ -1080,12 +1107,8 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
     if ((rc = launch_conv(B, B_GW1, B_GX, true, B_GXP, B_GXR, B_GHALO, 2, s))) return rc;
     if ((rc = launch_xsolve(B, B_GX, B_GCP, B_F, -1, s))) return rc;   // C' of step t - 1
   }
-  if (T > 1) {                   // C' of the start was written into buffer 0
-    SlotSet st;
-    st.add(B_GC, cbuf[0]);
-    st.add(B_GCP, cbuf[1]);
-    if ((rc = launch_set_slots(B, st, s))) return rc;
-  }
+  // C' of the start was written into buffer 0
+  if (T > 0 && (rc = ring.at(T - 1, T, d, s, fill))) return rc;
   // start: C^0 = B^T B X0 + X0, X0 = up(Y_l)
   if ((rc = launch_conv(B, B_GC, B_GW1, false, -1, -1, -1, 0, s))) return rc;
   if ((rc = launch_conv(B, B_GW1, B_GX, true, B_GC, -1, -1, 0, s))) return rc;

@@ -738,10 +738,14 @@ int launch_groups(const Batch& B, Kind kind, const char* name, Kern kern, hipStr
   return NLPR_OK;
 }
 
-// Buffer slots of descriptor 0 re-pointed on the stream (one thread per slot).
-__global__ void set_slots_kernel(SceneDesc* sd, SlotSet set) {
-  const int i = threadIdx.x;
-  if (i < set.n) sd->buf[set.slot[i]] = set.ptr[i];
+// Descriptor 1 + blockIdx.x: descriptor 0 with the table's pointers.
+__global__ void __launch_bounds__(256) desc_ring_kernel(SceneDesc* sd, SlotTable t) {
+  static_assert(sizeof(SceneDesc) % 4 == 0, "whole words");
+  SceneDesc* to = sd + 1 + blockIdx.x;
+  for (unsigned i = threadIdx.x; i < sizeof(SceneDesc) / 4; i += 256)
+    reinterpret_cast<unsigned*>(to)[i] = reinterpret_cast<const unsigned*>(sd)[i];
+  __syncthreads();
+  if ((int)threadIdx.x < t.n) to->buf[t.slot[threadIdx.x]] = t.ptr[blockIdx.x][threadIdx.x];
 }
 
 // Descriptor 0 written from the kernel argument, one word per thread.
@@ -849,10 +853,9 @@ int launch_upsample_zero(const Batch& B, int yl, int t, hipStream_t s) {
   return launch_groups(B, KD_PLANE, "upsample_zero_kernel", upsample_zero_kernel, s, yl, t);
 }
 
-int launch_set_slots(const Batch& B, const SlotSet& set, hipStream_t s) {
-  if (set.n <= 0) return NLPR_OK;
-  hipLaunchKernelGGL(set_slots_kernel, dim3(1), dim3(64), 0, s, B.d_desc, set);
-  NLPR_LAUNCH_CHECK("set_slots_kernel");
+int launch_desc_ring(const Batch& B, const SlotTable& t, hipStream_t s) {
+  hipLaunchKernelGGL(desc_ring_kernel, dim3(t.count), dim3(256), 0, s, B.d_desc, t);
+  NLPR_LAUNCH_CHECK("desc_ring_kernel");
   return NLPR_OK;
 }
 

@@ -206,7 +206,7 @@ struct Batch {
   size_t ws_bytes = 0;
   void* arena = nullptr;           // work-item tables, descriptors, flag, counters
   std::vector<int2> tables;        // the tables while the batch is built
-  SceneDesc* d_desc = nullptr;     // device descriptors, one per scene
+  SceneDesc* d_desc = nullptr;     // device descriptors, one per scene (and kDescRing more)
   SceneDesc* h_desc = nullptr;     // pinned staging copy (more than one scene)
   std::vector<SceneDesc> uploaded; // what d_desc holds
   bool desc_valid = false;
@@ -349,17 +349,18 @@ struct PuSlots {
   int x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo;
 };
 int launch_pupdate(const Batch& B, const PuSlots& sl, hipStream_t s);
-// Re-point buffer slots of the descriptor of scene 0 on the stream: kernels enqueued after it
-// see the new buffers.  The reverse-mode passes move through their checkpoints this way.
-struct SlotSet {
-  int n = 0;
+// Descriptors for the iterations of a reverse-mode pass, which moves through its checkpoints by
+// re-pointing buffer slots: copies of the descriptor of scene 0, each with its own pointers in
+// up to six slots, kDescRing at a time behind it.  (A launch before each iteration that
+// re-pointed the slots of the one descriptor took 4.5 us and its place in the queue twice per
+// iteration: gradient of 256 x 256 x 31 5.15 -> 5.04 ms.)
+constexpr int kDescRing = 32;
+struct SlotTable {
+  int n = 0, count = 0;            // slots, descriptors
   int slot[6];
-  void* ptr[6];
-  void add(int sl, void* p) {      // at most 6 (the callers add 2, 4 or 6)
-    if (n < 6) { slot[n] = sl; ptr[n] = p; ++n; }
-  }
+  void* ptr[kDescRing][6];
 };
-int launch_set_slots(const Batch& B, const SlotSet& set, hipStream_t s);
+int launch_desc_ring(const Batch& B, const SlotTable& t, hipStream_t s);
 int launch_set_desc(const Batch& B, const SceneDesc& d, hipStream_t s);   // scene 0's descriptor
 int lh_class(int Lh);                // pupdate template class of a guide-band count: 1, 4 or 16
 // threads per pixel of a P-update launch over `pixels` pixels in all: 4 (bands split) below

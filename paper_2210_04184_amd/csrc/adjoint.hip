@@ -12,6 +12,7 @@
 // The derivative of clip is 1 inside (|V| < mu) and 0 outside, where clip = +-mu moves with
 // mu instead.  All sums run in a fixed order (no atomics): gradients repeat bit for bit.
 #include "nlpr_internal.h"
+#include "pupdate.h"
 
 namespace nlpr {
 namespace {
@@ -22,20 +23,24 @@ __device__ __forceinline__ int wrapg(int a, int m) {
 }
 // Sum of v[k] over the 4 waves of the workgroup, in a fixed order; thread 0 gets it.
 template <int N>
-__device__ __forceinline__ void block_sum256(double (&v)[N]) {
-  __shared__ double red[N][4];
+__device__ __forceinline__ void block_sum256(double (&v)[N], double* red) {
 #pragma unroll
   for (int k = 0; k < N; ++k)
     for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_down(v[k], off, 64);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (lane == 0)
 #pragma unroll
-    for (int k = 0; k < N; ++k) red[k][w] = v[k];
+    for (int k = 0; k < N; ++k) red[4 * k + w] = v[k];
   __syncthreads();
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = ((red[k][0] + red[k][1]) + red[k][2]) + red[k][3];
+    for (int k = 0; k < N; ++k) v[k] = ((red[4 * k] + red[4 * k + 1]) + red[4 * k + 2]) + red[4 * k + 3];
   __syncthreads();
+}
+template <int N>
+__device__ __forceinline__ void block_sum256(double (&v)[N]) {
+  __shared__ double red[4 * N];
+  block_sum256<N>(v, red);
 }
 
 // ------------------------------------------------------------------------ sweep adjoint
@@ -78,10 +83,10 @@ __device__ __forceinline__ void block_sum256(double (&v)[N]) {
 // ahead (128 VGPRs) was best: 3 ahead takes 140 VGPRs and 68 us, 4 ahead 64 us, 3 ahead held
 // to 128 VGPRs spills and takes 75 us.
 template <int K, bool FIRST, bool CACHED>
-__global__ void __launch_bounds__(256, K <= 1 ? 4 : 1)
-sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int cb_s,
-                 const uint8_t* codes, int sb_s, int xr_s, int halo_s, int mup_s,
-                 const uint8_t* pcodes, int cbp_s) {
+__device__ __forceinline__ void
+sweep_bwd_body(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int cb_s,
+               const uint8_t* codes, int sb_s, int xr_s, int halo_s, int mup_s,
+               const uint8_t* pcodes, int cbp_s) {
   constexpr int NT = 256;
   constexpr int KW = 2 * K + 1;
   constexpr int NP = KW * KW;
@@ -372,6 +377,15 @@ sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ item
   }
 }
 
+template <int K, bool FIRST, bool CACHED>
+__global__ void __launch_bounds__(256, K <= 1 ? 4 : 1)
+sweep_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int cb_s,
+                 const uint8_t* codes, int sb_s, int xr_s, int halo_s, int mup_s,
+                 const uint8_t* pcodes, int cbp_s) {
+  sweep_bwd_body<K, FIRST, CACHED>(sd, items, cb_s, codes, sb_s, xr_s, halo_s, mup_s, pcodes,
+                                   cbp_s);
+}
+
 // mu'(tau, i) = sum over bands and over the tiles whose extended rows cover image row i of
 // the partial tiles.  One thread per (tau, pixel).
 __global__ void __launch_bounds__(256)
@@ -420,7 +434,7 @@ template <int LHM>
 __device__ __forceinline__ double pupdate_bwd_write(
     const gfloat* __restrict__ BX, const gfloat* __restrict__ Yl, const gfloat* __restrict__ L1,
     gfloat* __restrict__ W1b, const gfloat* __restrict__ W2b, gfloat* __restrict__ L1b,
-    gfloat* __restrict__ Xp, gfloat* __restrict__ GYl, const gfloat* __restrict__ R,
+    gfloat* __restrict__ Xp, gfloat* __restrict__ GYl, cfloat* R,
     const float (&v)[LHM], size_t plane,
     size_t lplane, size_t lj, bool sampled, int Lh, float inv, float rr, int c0, int c1, int j) {
   double acc = 0.0;
@@ -454,7 +468,7 @@ template <int LHM, int KB>
 __device__ __forceinline__ double pupdate_bwd_write_kept(
     const gfloat* __restrict__ BX, const gfloat* __restrict__ Yl, const gfloat* __restrict__ L1,
     gfloat* __restrict__ W1b, const float (&w2k)[KB], gfloat* __restrict__ L1b,
-    gfloat* __restrict__ Xp, gfloat* __restrict__ GYl, const gfloat* __restrict__ R,
+    gfloat* __restrict__ Xp, gfloat* __restrict__ GYl, cfloat* R,
     const float (&v)[LHM], size_t plane,
     size_t lplane, size_t lj, bool sampled, int Lh, float inv, float rr, int c0, int c1, int j) {
   float w1a[KB], l1ba[KB], yla[KB], bxa[KB], l1a[KB], gya[KB];
@@ -502,30 +516,25 @@ __device__ __forceinline__ double pupdate_bwd_write_kept(
 // arithmetic and its order are those of the band loops.
 constexpr int kPbKeep = 8;
 template <int LHM, int PB_NC, bool KEEP>
-__global__ void __launch_bounds__(256)
-pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
-                   int bx_s, int yl_s, int yh_s, int l1_s, int l2_s, int w1b_s, int w2b_s,
-                   int l1b_s, int xp_s, int gyl_s, int gyh_s, int part_s) {
+__device__ __forceinline__ void pupdate_bwd_body(const SceneDesc& S, int item, int sub,
+                                                 const PbSlots& sl, float* part,
+                                                 double* red) {
   constexpr int PX = 256 / PB_NC;          // pixels of the workgroup
-  __shared__ float part[PB_NC > 1 ? PB_NC : 1][PB_NC > 1 ? LHM : 1][PB_NC > 1 ? PX : 1];
-  const int2 it = work_item(items, blockIdx.x / PB_NC);
-  const int sub = blockIdx.x % PB_NC;
-  const SceneDesc& S = sd[it.x];
   const int p = S.p, q = S.q, L = S.L, Lh = S.Lh, d = S.d;
   const size_t plane = (size_t)p * q;
   // the band share is uniform over a wave; readfirstlane lets the band loops index R and G
   // with scalar loads
   const int pix = threadIdx.x & (PX - 1);
   const int ch = PB_NC == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PX);
-  const int j = it.y * 256 + sub * PX + pix;
+  const int j = item * 256 + sub * PX + pix;
   const bool act = j < (int)plane;
   const int c0 = (L * ch) / PB_NC, c1 = (L * (ch + 1)) / PB_NC;
-  const gfloat* X = gslot<const gfloat>(S, x_s);
-  const gfloat* L2 = gslot<const gfloat>(S, l2_s);
-  const gfloat* W2b = gslot<const gfloat>(S, w2b_s);
-  const gfloat* Xo = gslot<const gfloat>(S, xp_s);   // X' of the step before = -Lambda2''
-  const gfloat* R = as_global(S.R);
-  const gfloat* G = as_global(S.G);
+  const gfloat* X = gslot<const gfloat>(S, sl.x);
+  const gfloat* L2 = gslot<const gfloat>(S, sl.l2);
+  const gfloat* W2b = gslot<const gfloat>(S, sl.w2b);
+  const gfloat* Xo = gslot<const gfloat>(S, sl.xp);   // X' of the step before = -Lambda2''
+  cfloat* R = as_constant(S.R);
+  cfloat* G = as_constant(S.G);
   float rp[LHM], sp[LHM];
 #pragma unroll
   for (int h = 0; h < LHM; ++h) rp[h] = sp[h] = 0.f;
@@ -577,38 +586,38 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
     }
   } else {
 #pragma unroll
-    for (int h = 0; h < LHM; ++h) part[ch][h][pix] = rp[h];
+    for (int h = 0; h < LHM; ++h) part[(ch * LHM + h) * PX + pix] = rp[h];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < LHM; ++h) {
       float a = 0.f;
 #pragma unroll
-      for (int k = 0; k < PB_NC; ++k) a += part[k][h][pix];
+      for (int k = 0; k < PB_NC; ++k) a += part[(k * LHM + h) * PX + pix];
       res[h] = a;
     }
     __syncthreads();
 #pragma unroll
-    for (int h = 0; h < LHM; ++h) part[ch][h][pix] = sp[h];
+    for (int h = 0; h < LHM; ++h) part[(ch * LHM + h) * PX + pix] = sp[h];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < LHM; ++h) {
       float a = 0.f;
 #pragma unroll
-      for (int k = 0; k < PB_NC; ++k) a += part[k][h][pix];
+      for (int k = 0; k < PB_NC; ++k) a += part[(k * LHM + h) * PX + pix];
       sv[h] = a;
     }
   }
   double acc[2] = {0.0, 0.0};
   if (act) {
-    const gfloat* BX = gslot<const gfloat>(S, bx_s);
-    const gfloat* Yl = gslot<const gfloat>(S, yl_s);
-    const gfloat* Yh = gslot<const gfloat>(S, yh_s);
-    const gfloat* L1 = gslot<const gfloat>(S, l1_s);
-    gfloat* W1b = gslot<gfloat>(S, w1b_s);
-    gfloat* L1b = gslot<gfloat>(S, l1b_s);
-    gfloat* Xp = gslot<gfloat>(S, xp_s);
-    gfloat* GYl = gslot<gfloat>(S, gyl_s);
-    gfloat* GYh = gslot<gfloat>(S, gyh_s);
+    const gfloat* BX = gslot<const gfloat>(S, sl.bx);
+    const gfloat* Yl = gslot<const gfloat>(S, sl.yl);
+    const gfloat* Yh = gslot<const gfloat>(S, sl.yh);
+    const gfloat* L1 = gslot<const gfloat>(S, sl.l1);
+    gfloat* W1b = gslot<gfloat>(S, sl.w1b);
+    gfloat* L1b = gslot<gfloat>(S, sl.l1b);
+    gfloat* Xp = gslot<gfloat>(S, sl.xp);
+    gfloat* GYl = gslot<gfloat>(S, sl.gyl);
+    gfloat* GYh = gslot<gfloat>(S, sl.gyh);
     const float inv = S.inv_1prho, rr = S.rho * S.inv_1prho;   // 1/(1+rho), rho/(1+rho)
     const int i1 = j / q, i2 = j - (j / q) * q;
     const bool sampled = (i1 % d == 0) && (i2 % d == 0);
@@ -648,12 +657,43 @@ pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ it
       acc[0] = pupdate_bwd_write<LHM>(BX, Yl, L1, W1b, W2b, L1b, Xp, GYl, R, v, plane,
                                       lplane, lj, sampled, Lh, inv, rr, c0, c1, j);
   }
-  block_sum256<2>(acc);
+  block_sum256<2>(acc, red);
   if (threadIdx.x == 0) {
-    gdouble* prt = gslot<gdouble>(S, part_s) + 2 * ((size_t)it.y * PB_NC + sub);
+    gdouble* prt = gslot<gdouble>(S, sl.part) + 2 * ((size_t)item * PB_NC + sub);
     prt[0] += acc[0];
     prt[1] += acc[1];
   }
+}
+
+template <int LHM, int PB_NC, bool KEEP>
+__global__ void __launch_bounds__(256)
+pupdate_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, PbSlots sl) {
+  __shared__ float part[pupdate_lds_floats(LHM, PB_NC)];
+  __shared__ double red[8];
+  const int2 it = work_item(items, blockIdx.x / PB_NC);
+  pupdate_bwd_body<LHM, PB_NC, KEEP>(sd[it.x], it.y, blockIdx.x % PB_NC, sl, part, red);
+}
+
+// The sweep's adjoint (the first nsw workgroups) and the P-update's (the rest), which write
+// disjoint buffers, in one launch, as in the forward iteration.  Gradient
+// of 256 x 256 x 31, 20 iterations: 5.07 -> 4.90 ms (the P-update alone took 24 us per iteration);
+// of 96 x 96 x 8, 10 iterations: 1.39 -> 1.33 ms.
+template <int K, bool CACHED>
+__global__ void __launch_bounds__(256, K <= 1 ? 4 : 1)
+sweep_pb_bwd_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int cb_s,
+                    const uint8_t* codes, int sb_s, int xr_s, int halo_s, int mup_s,
+                    const uint8_t* pcodes, int cbp_s, PbSlots sl, int nsw, int lhm) {
+  const int b = (int)blockIdx.x - nsw;
+  if (b >= 0) {
+    extern __shared__ float4 lds4[];
+    double* red = reinterpret_cast<double*>(lds4);
+    float* part = reinterpret_cast<float*>(red + 8);
+    if (lhm == 1) pupdate_bwd_body<1, 4, true>(sd[0], b / 4, b % 4, sl, part, red);
+    else pupdate_bwd_body<4, 4, true>(sd[0], b / 4, b % 4, sl, part, red);
+    return;
+  }
+  sweep_bwd_body<K, false, CACHED>(sd, items, cb_s, codes, sb_s, xr_s, halo_s, mup_s, pcodes,
+                                   cbp_s);
 }
 
 // ------------------------------------------------------------------ weights adjoint
@@ -838,8 +878,14 @@ int launch_kind(const Batch& B, Kind kind, const char* name, Kern kern, hipStrea
 template <int K, bool CACHED>
 int launch_sbwd_policy(const Batch& B, const Group& g, size_t lds, int cb, const uint8_t* codes,
                        int sb, int xr, int halo, int mup, const uint8_t* pcodes, int cbp,
-                       hipStream_t s) {
-  if (pcodes) {
+                       const PbSlots* pb, hipStream_t s) {
+  if (pb) {
+    const Group& gp = B.groups[KD_PIXEL][0];
+    hipLaunchKernelGGL((sweep_pb_bwd_kernel<K, CACHED>), dim3(g.nitems + 4 * gp.nitems), dim3(256),
+                       std::max(lds, 8 * sizeof(double) + sizeof(float) * pupdate_lds_floats(4, 4)),
+                       s, B.d_desc, g.d_items, cb, codes, sb, xr, halo, mup, pcodes, cbp, *pb, g.nitems,
+                       gp.key0);
+  } else if (pcodes) {
     hipLaunchKernelGGL((sweep_bwd_kernel<K, false, CACHED>), dim3(g.nitems), dim3(256), lds, s,
                        B.d_desc, g.d_items, cb, codes, sb, xr, halo, mup, pcodes, cbp);
   } else {
@@ -852,15 +898,18 @@ int launch_sbwd_policy(const Batch& B, const Group& g, size_t lds, int cb, const
 
 template <int K>
 int launch_sbwd(const Batch& B, const Group& g, size_t lds, int cb, const uint8_t* codes, int sb,
-                int xr, int halo, int mup, const uint8_t* pcodes, int cbp, hipStream_t s) {
+                int xr, int halo, int mup, const uint8_t* pcodes, int cbp, const PbSlots* pb,
+                hipStream_t s) {
   return g.policy == kSweepCached
-             ? launch_sbwd_policy<K, true>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s)
-             : launch_sbwd_policy<K, false>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s);
+             ? launch_sbwd_policy<K, true>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s)
+             : launch_sbwd_policy<K, false>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s);
 }
 
 template <int K>
 int sbwd_attr() {
-  const void* kern[4] = {reinterpret_cast<const void*>(sweep_bwd_kernel<K, true, true>),
+  const void* kern[6] = {reinterpret_cast<const void*>(sweep_pb_bwd_kernel<K, true>),
+                         reinterpret_cast<const void*>(sweep_pb_bwd_kernel<K, false>),
+                         reinterpret_cast<const void*>(sweep_bwd_kernel<K, true, true>),
                          reinterpret_cast<const void*>(sweep_bwd_kernel<K, true, false>),
                          reinterpret_cast<const void*>(sweep_bwd_kernel<K, false, true>),
                          reinterpret_cast<const void*>(sweep_bwd_kernel<K, false, false>)};
@@ -901,25 +950,30 @@ int sweep_bwd_prepare(int K) {
 }
 
 int launch_sweep_bwd(const Batch& B, int cb, const uint8_t* codes, int sb, int xr, int halo,
-                     int mup, const uint8_t* pcodes, int cbp, hipStream_t s) {
+                     int mup, const uint8_t* pcodes, int cbp, const PbSlots& sl, hipStream_t s) {
   const Plan& P = *B.scenes[0];
   const size_t lds = sweep_bwd_lds(P);
+  // in one launch after the first step: four threads per pixel, their bands in registers
+  const auto& gp = B.groups[KD_PIXEL];
+  const bool both = pcodes && B.groups[KD_SWEEP].size() == 1 && gp.size() == 1 &&
+                    gp[0].key1 == 4 && gp[0].key0 <= 4 && ceil_div(P.Lx, 4) <= kPbKeep;
+  const PbSlots* pb = both ? &sl : nullptr;
   for (const Group& g : B.groups[KD_SWEEP]) {
     if (!g.nitems) continue;
     int rc;
     switch (g.key0) {
-      case 0: rc = launch_sbwd<0>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s); break;
-      case 1: rc = launch_sbwd<1>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s); break;
-      case 2: rc = launch_sbwd<2>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s); break;
-      case 3: rc = launch_sbwd<3>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s); break;
-      case 4: rc = launch_sbwd<4>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, s); break;
+      case 0: rc = launch_sbwd<0>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;
+      case 1: rc = launch_sbwd<1>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;
+      case 2: rc = launch_sbwd<2>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;
+      case 3: rc = launch_sbwd<3>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;
+      case 4: rc = launch_sbwd<4>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;
       default:
         set_error("sweep adjoint: unsupported patch radius");
         return NLPR_ERR_UNSUPPORTED_SHAPE;
     }
     if (rc) return rc;
   }
-  return NLPR_OK;
+  return both ? (int)NLPR_OK : launch_pupdate_bwd(B, sl, s);
 }
 
 // Threads per pixel, and with them workgroups and partial sums per work item.
@@ -933,34 +987,27 @@ int launch_mubar_reduce(const Batch& B, int mup, int mub, hipStream_t s) {
 }
 
 template <int LHM, int NC>
-void launch_pb(const Batch& B, const Group& g, int x, int bx, int yl, int yh, int l1, int l2,
-               int w1b, int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s) {
+void launch_pb(const Batch& B, const Group& g, const PbSlots& sl, hipStream_t s) {
   // the reverse mode takes one scene: its bands per thread decide the variant
-  if (ceil_div(B.scenes[0]->Lx, NC) <= kPbKeep)
-    hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, true>), dim3(g.nitems * NC), dim3(256), 0,
-                       s, B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
-                       gyl, gyh, part);
-  else
-    hipLaunchKernelGGL((pupdate_bwd_kernel<LHM, NC, false>), dim3(g.nitems * NC), dim3(256), 0,
-                       s, B.d_desc, items_of(B, g), x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp,
-                       gyl, gyh, part);
+  auto kern = ceil_div(B.scenes[0]->Lx, NC) <= kPbKeep ? pupdate_bwd_kernel<LHM, NC, true>
+                                                       : pupdate_bwd_kernel<LHM, NC, false>;
+  hipLaunchKernelGGL(kern, dim3(g.nitems * NC), dim3(256), 0, s, B.d_desc, items_of(B, g), sl);
 }
 
-int launch_pupdate_bwd(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1b,
-                       int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s) {
+int launch_pupdate_bwd(const Batch& B, const PbSlots& sl, hipStream_t s) {
   for (const Group& g : B.groups[KD_PIXEL]) {
     if (!g.nitems) continue;
     const bool split = g.key1 == 4;
-#define NLPR_PB(LHM, NC) \
-  launch_pb<LHM, NC>(B, g, x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp, gyl, gyh, part, s)
     if (g.key0 == 1) {
-      if (split) NLPR_PB(1, 4); else NLPR_PB(1, 1);
+      if (split) launch_pb<1, 4>(B, g, sl, s);
+      else launch_pb<1, 1>(B, g, sl, s);
     } else if (g.key0 == 4) {
-      if (split) NLPR_PB(4, 4); else NLPR_PB(4, 1);
+      if (split) launch_pb<4, 4>(B, g, sl, s);
+      else launch_pb<4, 1>(B, g, sl, s);
     } else {
-      if (split) NLPR_PB(kMaxLh, 2); else NLPR_PB(kMaxLh, 1);   // registers: 2 at most
+      if (split) launch_pb<kMaxLh, 2>(B, g, sl, s);   // registers: 2 at most
+      else launch_pb<kMaxLh, 1>(B, g, sl, s);
     }
-#undef NLPR_PB
     NLPR_LAUNCH_CHECK("pupdate_bwd_kernel");
   }
   return NLPR_OK;

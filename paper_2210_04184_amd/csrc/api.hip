@@ -1096,13 +1096,12 @@ int grad_backward(Batch& B, const float* Yl, const float* Yh, const float* dZ, v
   for (int t = T - 1; t >= 1; --t) {
     if ((rc = ring.at(T - 1 - t, T, d, s, fill))) return rc;
     if ((rc = launch_conv(B, B_GC, B_GW1, false, -1, -1, -1, 0, s))) return rc;   // W1' = B C'
-    if (reg && (rc = launch_sweep_bwd(B, B_GC, ck_codes(ck, G, T, t), B_GSIG, B_GXR, B_GHALO,
-                                      B_GMUP, t + 1 < T ? ck_codes(ck, G, T, t + 1) : nullptr,
-                                      B_GCP, s)))
-      return rc;
-    if ((rc = launch_pupdate_bwd(B, B_Z, B_BX, B_YL, B_YH, B_L1, B_L2, B_GW1, B_GC, B_GL1, B_GXP,
-                                 B_GYL, B_GYH, B_GPART, s)))
-      return rc;
+    const PbSlots pb{B_Z,  B_BX,  B_YL,  B_YH,  B_L1,  B_L2,   B_GW1,
+                     B_GC, B_GL1, B_GXP, B_GYL, B_GYH, B_GPART};
+    rc = reg ? launch_sweep_bwd(B, B_GC, ck_codes(ck, G, T, t), B_GSIG, B_GXR, B_GHALO, B_GMUP,
+                                t + 1 < T ? ck_codes(ck, G, T, t + 1) : nullptr, B_GCP, pb, s)
+             : launch_pupdate_bwd(B, pb, s);
+    if (rc) return rc;
     // X' = B^T BX' + X'(P-update) + X'(sweep) (+ halo rows)
     if ((rc = launch_conv(B, B_GW1, B_GX, true, B_GXP, B_GXR, B_GHALO, 2, s))) return rc;
     if ((rc = launch_xsolve(B, B_GX, B_GCP, B_F, -1, s))) return rc;   // C' of step t - 1

@@ -391,12 +391,14 @@ int sweep_bwd_prepare(int K);
 // codes: the forward sweep's threshold branches of the iteration (launch_sweep's codes);
 // pcodes, cbp: those of the iteration whose backward step ran last and its C' (null on the
 // first backward step, whose incoming Sigma'' is zero)
+struct PbSlots {                   // buffer slots of the P-update's adjoint
+  int x, bx, yl, yh, l1, l2, w1b, w2b, l1b, xp, gyl, gyh, part;
+};
 int launch_sweep_bwd(const Batch& B, int cb, const uint8_t* codes, int sb, int xr, int halo,
-                     int mup, const uint8_t* pcodes, int cbp, hipStream_t s);
+                     int mup, const uint8_t* pcodes, int cbp, const PbSlots& sl, hipStream_t s);
 int pupdate_bwd_split(const Plan& P);
 int launch_mubar_reduce(const Batch& B, int mup, int mub, hipStream_t s);
-int launch_pupdate_bwd(const Batch& B, int x, int bx, int yl, int yh, int l1, int l2, int w1b,
-                       int w2b, int l1b, int xp, int gyl, int gyh, int part, hipStream_t s);
+int launch_pupdate_bwd(const Batch& B, const PbSlots& sl, hipStream_t s);
 int launch_weights_bwd(const Batch& B, int yh, int mub, int eb, int part, int w0, hipStream_t s);
 int launch_yh_bwd(const Batch& B, int yh, int eb, int gyh, hipStream_t s);
 int launch_upsample_bwd(const Batch& B, int x0b, int gyl, hipStream_t s);

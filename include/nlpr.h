@@ -276,7 +276,8 @@ typedef enum nlpr_region {
                              element on the threshold is -mu (V > 0) or +mu (V < 0) and is not
                              stored; for an item with any element off the threshold ("open")
                              the 4 values -Sigma' = clip(V, +-mu) are stored, packed at the
-                             start of the item's segment in item order.                      */
+                             start of the item's segment in item order.  The slots behind
+                             them hold nothing (up to three are written with each run).      */
   NLPR_REGION_MU = 1,     /* mu [Npairs][p][q] = lambda * omega_{i tau} / rho, the thresholds         */
   NLPR_REGION_C = 2,      /* C [L][p][q], right-hand side of eq. (x_linear_system_main)                */
   NLPR_REGION_LAMBDA1 = 3,/* Lambda1 [L][p][q]                                                       */
@@ -378,7 +379,7 @@ int nlpr_monitor(const nlpr_plan* plan, double* trace, int32_t cap, int32_t* n);
  *
  * nlpr_grad_sizes: bytes of the checkpoint buffer and of the gradient workspace.  For
  *   t = 1 .. iters-1 the checkpoints hold X^t, B X^t, the Lambda1 and Lambda2 entering
- *   iteration t, and which branch of the threshold every dual element of its sweep took
+ *   iteration t (B X^t and Lambda1 at the sampled pixels), and which branch of the threshold every dual element of its sweep took
  *   (2 bits each: |V| < mu, V >= mu or V <= -mu; the adjoint needs nothing else of Sigma).
  *   They take (iters - 1) * (16 + Npairs |P| / 4) * L * p * q bytes, each part rounded up to
  *   a multiple of 256 (at least 256 in all).

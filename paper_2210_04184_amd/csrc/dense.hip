@@ -27,9 +27,12 @@ __device__ __forceinline__ int wrapi(int x, int n) {
 }
 
 // ------------------------------------------------------------------------- precompute
-// tw[m] = exp(-2 pi i m / n), in FP64, stored FP32.
-__global__ void twiddle_kernel(float2* tw, int n) {
+// tw[m] = exp(-2 pi i m / n), in FP64, stored FP32, for the rows' length (blockIdx.y = 0) and
+// the columns'.
+__global__ void twiddle_kernel(float2* twp, int p, float2* twq, int q) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  float2* tw = blockIdx.y ? twq : twp;
+  const int n = blockIdx.y ? q : p;
   if (m >= n) return;
   double s, c;
   sincospi(-2.0 * (double)m / (double)n, &s, &c);
@@ -40,34 +43,55 @@ __global__ void twiddle_kernel(float2* tw, int n) {
 // |d^_{tau 0}|^2 = 2 - 2 cos(2 pi (u tau1 / p + v tau2 / q)) and the sum over W equal to
 // twice the sum over W+ (the tau = 0 term vanishes).  Phases are reduced exactly in
 // integers before the FP64 sine/cosine.
-__global__ void den_kernel(float* invden, int p, int q, const float* blur, int r,
-                           const int2* taus, int npairs, int npatch) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  const int u = blockIdx.y;
-  if (v >= q) return;
-  double br = 0.0, bi = 0.0;
+// Bound by the FP64 sines: a workgroup takes FREQ frequencies and spreads the terms of each
+// over 256 / FREQ threads, which leave them in LDS; one thread per frequency adds them up in
+// term order.  With one thread per frequency 128 x 128 had one wave per CU, and two 64-bit
+// remainders per term: 47.7 us, now 14.4; 96 x 96 31.8 and 9.3; 1024 x 1024 438 and 437.  FREQ = 64 where
+// the frequencies alone fill the GPU: the adding is done by a whole wave (1024 x 1024 with 16:
+// 392 us).
+template <int FREQ>
+__global__ void __launch_bounds__(256)
+den_kernel(float* invden, int p, int q, const float* blur, int r, const int2* taus, int npairs,
+           int npatch) {
+  constexpr int LANES = 256 / FREQ, TERMS = 1536 / FREQ;
+  __shared__ double cs[FREQ][TERMS + 1], sn[FREQ][TERMS + 1];
+  const int f = threadIdx.x / LANES, lane = threadIdx.x % LANES;
+  const int u = blockIdx.y, v = min(blockIdx.x * FREQ + f, q - 1);
   const int w = 2 * r + 1;
-  for (int m1 = -r; m1 <= r; ++m1) {
-    const long a = (((long)u * m1) % p + p) % p;
-    for (int m2 = -r; m2 <= r; ++m2) {
-      const long b = (((long)v * m2) % q + q) % q;
-      const double ph = -2.0 * ((double)a / p + (double)b / q);
-      double sn, cs;
-      sincospi(ph, &sn, &cs);
-      const double tap = (double)blur[(m1 + r) * w + (m2 + r)];
-      br += tap * cs;
-      bi += tap * sn;
+  double br = 0.0, bi = 0.0;
+  for (int k0 = 0; k0 < w * w; k0 += TERMS) {
+    const int n = min(TERMS, w * w - k0);
+    for (int k = lane; k < n; k += LANES) {
+      const int m1 = (k0 + k) / w - r, m2 = (k0 + k) % w - r;
+      const int a = wrapi(u * m1, p), b = wrapi(v * m2, q);
+      sincospi(-2.0 * ((double)a / p + (double)b / q), &sn[f][k], &cs[f][k]);
     }
+    __syncthreads();
+    if (threadIdx.x < FREQ)
+      for (int k = 0; k < n; ++k) {
+        const double tap = (double)blur[k0 + k];
+        br += tap * cs[threadIdx.x][k];
+        bi += tap * sn[threadIdx.x][k];
+      }
+    __syncthreads();
   }
   double dsum = 0.0;
-  for (int n = 0; n < npairs; ++n) {
-    const int2 t = taus[n];
-    const long a = (((long)u * t.x) % p + p) % p;
-    const long b = (((long)v * t.y) % q + q) % q;
-    dsum += 2.0 - 2.0 * cospi(2.0 * ((double)a / p + (double)b / q));
+  for (int n0 = 0; n0 < npairs; n0 += TERMS) {
+    const int n = min(TERMS, npairs - n0);
+    for (int k = lane; k < n; k += LANES) {
+      const int2 t = taus[n0 + k];
+      const int a = wrapi(u * t.x, p), b = wrapi(v * t.y, q);
+      cs[f][k] = cospi(2.0 * ((double)a / p + (double)b / q));
+    }
+    __syncthreads();
+    if (threadIdx.x < FREQ)
+      for (int k = 0; k < n; ++k) dsum += 2.0 - 2.0 * cs[threadIdx.x][k];
+    __syncthreads();
   }
+  const int vt = blockIdx.x * FREQ + threadIdx.x;
+  if (threadIdx.x >= FREQ || vt >= q) return;
   const double den = 1.0 + br * br + bi * bi + (double)npatch * 2.0 * dsum;
-  invden[(size_t)u * q + v] = (float)(1.0 / (den * (double)p * (double)q));
+  invden[(size_t)u * q + vt] = (float)(1.0 / (den * (double)p * (double)q));
 }
 
 // Tables of the X-update with S inside the system (fused-S).  Per band the system is
@@ -816,12 +840,12 @@ int pixel_blocks(const Plan& P) { return ceil_div(P.prm.p * P.prm.q, 256); }
 // ---------------------------------------------------------------------------- launches
 int launch_precompute(Plan& P) {
   const int p = P.prm.p, q = P.prm.q;
-  hipLaunchKernelGGL(twiddle_kernel, dim3(ceil_div(p, 256)), dim3(256), 0, nullptr, P.d_tw_p, p);
+  hipLaunchKernelGGL(twiddle_kernel, dim3(ceil_div(std::max(p, q), 256), 2), dim3(256), 0, nullptr,
+                     P.d_tw_p, p, P.d_tw_q, q);
   NLPR_LAUNCH_CHECK("twiddle_kernel");
-  hipLaunchKernelGGL(twiddle_kernel, dim3(ceil_div(q, 256)), dim3(256), 0, nullptr, P.d_tw_q, q);
-  NLPR_LAUNCH_CHECK("twiddle_kernel");
-  hipLaunchKernelGGL(den_kernel, dim3(ceil_div(q, 128), p), dim3(128), 0, nullptr, P.d_invden, p,
-                     q, P.d_blur, P.prm.blur_radius, P.d_taus, P.npairs, P.npatch);
+  const bool many = (size_t)p * q >= (size_t)1 << 17;
+  hipLaunchKernelGGL(many ? den_kernel<64> : den_kernel<16>, dim3(ceil_div(q, many ? 64 : 16), p),
+                     dim3(256), 0, nullptr, P.d_invden, p, q, P.d_blur, P.prm.blur_radius, P.d_taus, P.npairs, P.npatch);
   NLPR_LAUNCH_CHECK("den_kernel");
   if (P.d_E) {
     hipLaunchKernelGGL(subspace_kernel, dim3(1), dim3(256), 0, nullptr, P.d_E, P.d_R, P.prm.L, P.Lx,

@@ -725,9 +725,11 @@ int enqueue_solve(Batch& B, bool resume, hipStream_t s) {
       NLPR_HIP_TRY(hipStreamWaitEvent(B.side, B.fork_ev, 0));
       sp = B.side;
     }
-    // B X goes straight into W1, where the P-update changes the sampled pixels only; a monitor
-    // record reads B X beside W1.  (fused-S needs B X only for the monitor's data term.)
-    const int bx = fused || mon ? B_BX : B_W1;
+    // B X goes straight into W1, where the P-update changes the sampled pixels only, Lambda1
+    // being zero on the others; a monitor record reads B X beside W1, and a resumed solve takes
+    // Lambda1 from the caller's workspace, where it may hold any value on every pixel.  (fused-S
+    // needs B X only for the monitor's data term.)
+    const int bx = fused || mon || resume ? B_BX : B_W1;
     if (!fused || mon) {
       StageTimer tm(B, sp, NLPR_STAGE_BLUR);
       if ((rc = launch_conv(B, B_Z, bx, false, -1, -1, -1, 0, sp))) return rc;

@@ -340,11 +340,11 @@ int launch_init(const Batch& B, int yl, int ylp, int x0, int l1, int l2, int w2,
 // parts 1 .. psplit-1 (slot B_CSPLIT) and halo parts are then added as well
 int launch_conv(const Batch& B, int in, int out, bool transpose, int add1, int add2, int halo,
                 int reg_mask, hipStream_t s);
-// Lambda1, Lambda2 are read from slots l1, l2 and written to l1o, l2o (the same slots for an
-// update in place).  bx == w1: B X lies in W1 and only the sampled pixels' P1, Lambda1 and W1
-// are updated, the others being P1 + Lambda1 = B X with Lambda1 = 0 already.  bxo >= 0: the slot
-// that also takes B X where P1 is updated.
-// buffer slots of the P-update (bxo: -1, or where B X also goes)
+// Buffer slots of the P-update.  Lambda1, Lambda2 are read from slots l1, l2 and written to
+// l1o, l2o (the same slots for an update in place).  bx == w1: B X lies in W1 and only the
+// sampled pixels' P1, Lambda1 and W1 are updated, the others being P1 + Lambda1 = B X; the caller
+// knows their Lambda1 to be zero (a solve that started from zero keeps it so).  bxo >= 0: the
+// slot that also takes B X where P1 is updated.
 struct PuSlots {
   int x, bx, yl, yh, l1, l2, w1, w2, l1o, l2o, bxo;
 };

@@ -207,7 +207,11 @@ sweep_body(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int
   constexpr int D = K == 0 ? 6 : K == 1 ? 4 : 5, E = D;
   const int nplanes = (n_end - n_begin) * NP;
   const size_t base = tile_off + (size_t)n_begin * tstride;
-  constexpr bool RING = NP > D + E;
+  // The ring's indices are constants only where the planes of a shift are unrolled, which is
+  // past the compiler's limit for the 81 planes of 9 x 9 with branch codes: there the registers
+  // move on by one per plane (as a ring they lay in scratch memory: gradient of 256 x 256 x 16,
+  // 9x9/3x3, 6 iterations, 6.83 ms, like this 3.13 ms).
+  constexpr bool RING = NP > D + E && !(CODES && K > 3);
   uint8_t cq[RING ? NP : D + E + 1];   // code bytes of planes x .. x + D + E (kept as bytes: a
                                        // widening at the loop's back edge would wait)
   float4 sb[RING ? NP : D + 1];        // open float4s of planes x .. x + D

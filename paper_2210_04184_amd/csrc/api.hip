@@ -252,7 +252,7 @@ int scene_create(const nlpr_params& prm, const float* blur_host, const float* R_
     return cleanup(NLPR_ERR_HIP);
   }
   if ((rc = launch_precompute(*P))) return cleanup(rc);
-  if ((rc = autotune_fft(*P))) return cleanup(rc);
+  if ((rc = fft_prepare(*P)) || (rc = autotune_fft(*P))) return cleanup(rc);
   // workspace layout
   size_t off = 0;
   auto take = [&](int slot, size_t bytes) {

@@ -478,6 +478,8 @@ size_t rows_bytes(int q, int lpb) {
 size_t cols_bytes(int p, int cb, int d_fused) {
   return ((size_t)(cb + 1) * p + (d_fused > 0 ? (size_t)cb * (p / d_fused) : 0)) * sizeof(float2);
 }
+// one line with its padding takes more than 64 KiB from q = 3888 on
+size_t rows_max(int q) { return std::max(kFftLds, rows_bytes(q, 1)); }
 // a column group of fused-S is at least d columns: beyond 64 KiB by its partial sums at most
 size_t cols_max(int p, int d_fused) {
   return std::max(kFftLds, d_fused > 0 ? cols_bytes(p, d_fused, d_fused) : 0);
@@ -579,6 +581,24 @@ int launch_xsolve(const Batch& B, int c, int x, int f, int add, hipStream_t s) {
   return launch_rows(B, true, f, x, add, s);
 }
 
+// Allow the passes of an image size more dynamic LDS than the default limit where a single line
+// or column group needs it; before their launches and outside graph capture.
+int fft_prepare(const Plan& P) {
+  const void* kern[4] = {};
+  if (rows_max(P.prm.q) > kFftLds) {
+    kern[0] = reinterpret_cast<const void*>(fft_rows_fwd);
+    kern[1] = reinterpret_cast<const void*>(fft_rows_inv<false>);
+    kern[2] = reinterpret_cast<const void*>(fft_rows_inv<true>);
+  }
+  if (cols_max(P.prm.p, P.d_fia ? P.prm.d : 0) > kFftLds)
+    kern[3] = reinterpret_cast<const void*>(fft_cols_solve);
+  for (const void* k : kern)
+    if (k)
+      NLPR_HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kMaxSweepLds));
+  return NLPR_OK;
+}
+
 // Autotuner: time the row and column passes of one band pair for every admissible lines-
 // per-block / columns-per-block choice and keep the fastest; results are cached per
 // (device, p, q) for the life of the process.
@@ -626,14 +646,6 @@ int autotune_fft(Plan& P) {
     set_error("autotune: allocation failed");
     return NLPR_ERR_HIP;
   }
-  if (cols_max(p, dfu) > kFftLds &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(fft_cols_solve),
-                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)kMaxSweepLds) != hipSuccess) {
-    cleanup();
-    set_error("autotune: the column pass needs more LDS than a workgroup can have");
-    return NLPR_ERR_HIP;
-  }
   hipMemset(d_real, 0, 2 * tp * plane * sizeof(float));
   std::vector<int2> items(maxitems);
   for (int i = 0; i < maxitems; ++i) items[i] = make_int2(0, i);
@@ -673,7 +685,7 @@ int autotune_fft(Plan& P) {
     const int tpl = best.q_tpl;
     float tbest = 1e30f;
     for (int lpb = 1; lpb * tpl <= 1024; lpb *= 2) {
-      if (rows_bytes(q, lpb) > kFftLds) break;
+      if (rows_bytes(q, lpb) > rows_max(q)) break;
       const int bs = lines_block(tpl, lpb);
       h.fq_tpl = tpl;
       h.fq_lpb = lpb;

@@ -434,6 +434,7 @@ int sweep_policy(size_t state, int planes);
 int choose_pair_split(int blocks, int npairs);   // SweepShape.split for `blocks` (tile, band) pairs
 size_t sweep_sigma_bytes(const SweepShape& sh, int q, int L, int npairs, int npatch);
 int fft_block(int tpl);             // workgroup size of a line FFT with tpl threads per line
+int fft_prepare(const Plan& P);     // kernel attributes of the X-update; before its launches
 int autotune_fft(Plan& P);          // picks P.fft by timing candidates (cached per (p, q, d if fused))
 FftShape default_fft_shape(int p, int q, int d_fused);
 void batch_fft_shape(Plan& P);      // P.fft of a scene of a batch

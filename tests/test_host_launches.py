@@ -1,0 +1,55 @@
+"""What the host side launches, on the CPU: tests/c/host_launches.cpp runs the library on HIP
+runtime functions of its own, which print each launch in place of making it."""
+import os
+import shutil
+import subprocess
+from collections import namedtuple
+
+import pytest
+
+from paper_2210_04184_amd import build, nlpr
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+Launch = namedtuple("Launch", "phase kernel grid block lds limit table")
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not os.path.exists(nlpr.LIB_PATH) or not (shutil.which("hipcc") or
+                                                 os.path.exists("/opt/rocm/bin/hipcc")):
+        pytest.skip("needs libnlpr.so and hipcc")
+    exe = str(tmp_path_factory.mktemp("host") / "host_launches")
+    lib = os.path.dirname(nlpr.LIB_PATH)
+    flags = [f for f in build.HIP_FLAGS if f not in ("-O3", "-fPIC")]
+    res = subprocess.run([build.hipcc(), "--offload-host-only", "-x", "hip", *flags,
+                          os.path.join(HERE, "c", "host_launches.cpp"), "-o", exe, "-L", lib,
+                          "-lnlpr", "-Wl,-rpath," + lib], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+
+    def go(n=1, p=24, q=36, L=3, Lh=1, d=2, r=1, K=1, Sw=1, iters=3, flags=0, more=()):
+        """(launches, {phase: status})"""
+        args = [exe, *map(str, (n, p, q, L, Lh, d, r, K, Sw, iters, flags)), *more]
+        res = subprocess.run(args, capture_output=True, text=True, timeout=60)
+        assert res.returncode == 0, res.stderr
+        launches, status = [], {}
+        for line in res.stdout.splitlines():
+            f = line.split()
+            if f[1] == "status":
+                status[f[0]] = int(f[2])
+            else:
+                launches.append(Launch(f[0], f[1], *map(int, f[2:6]), f[6]))
+        return launches, status
+    return go
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("kw", [dict(), dict(q=3888, K=0), dict(q=4096, K=0), dict(p=4096, q=24),
+                                dict(p=4096, q=24, d=1, flags=nlpr.FUSED_S),
+                                dict(p=1536, q=24, d=4, flags=nlpr.FUSED_S),
+                                dict(q=972, K=4, Sw=8)],
+                         ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()) or "small")
+def test_dynamic_lds_is_within_each_kernels_limit(run, kw, n):
+    launches, status = run(n=n, **kw)
+    assert set(status.values()) == {nlpr.OK}
+    assert {"create", "solve"} <= {x.phase for x in launches}
+    assert [x for x in launches if x.lds > x.limit or x.limit > 160 * 1024] == []

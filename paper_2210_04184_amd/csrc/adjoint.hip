@@ -960,7 +960,8 @@ int launch_sweep_bwd(const Batch& B, int cb, const uint8_t* codes, int sb, int x
   const PbSlots* pb = both ? &sl : nullptr;
   for (const Group& g : B.groups[KD_SWEEP]) {
     if (!g.nitems) continue;
-    int rc;
+    int rc = check_table(g);
+    if (rc) return rc;
     switch (g.key0) {
       case 0: rc = launch_sbwd<0>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;
       case 1: rc = launch_sbwd<1>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s); break;

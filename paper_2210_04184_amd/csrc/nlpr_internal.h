@@ -253,6 +253,14 @@ void set_error(const std::string& msg);
     }                                                                               \
   } while (0)
 
+// The sweep and its adjoint index their table whatever it is: their items are in an order that
+// the workgroup index does not give (sweep_items).
+inline int check_table(const Group& g) {
+  if (g.d_items) return NLPR_OK;
+  set_error("sweep: no work-item table");
+  return NLPR_ERR_HIP;
+}
+
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Pointers read from a descriptor are generic (flat); kernels convert them to the global

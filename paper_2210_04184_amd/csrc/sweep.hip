@@ -761,6 +761,7 @@ bool sweep_pu(const Batch& B) {
 int launch_sweep_pu(const Batch& B, const PuSlots& sl, int x, int mu, int sig, int creg, int halo,
                     hipStream_t s, uint8_t* codes) {
   const Group &g = B.groups[KD_SWEEP][0], &gp = B.groups[KD_PIXEL][0];
+  if (const int rc = check_table(g)) return rc;
   switch (g.key0) {
     case 0: return launch_pu_k<0>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
     case 1: return launch_pu_k<1>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
@@ -831,7 +832,8 @@ int launch_sweep(const Batch& B, int x, int mu, int sig, int creg, int halo, boo
                  hipStream_t s, uint8_t* codes, unsigned long long* count) {
   for (const Group& g : B.groups[KD_SWEEP]) {
     if (!g.nitems) continue;
-    int rc;
+    int rc = check_table(g);
+    if (rc) return rc;
     switch (g.key0) {
 #define NLPR_SW(KK)                                                                            \
   case KK:                                                                                     \

@@ -53,3 +53,20 @@ def test_dynamic_lds_is_within_each_kernels_limit(run, kw, n):
     assert set(status.values()) == {nlpr.OK}
     assert {"create", "solve"} <= {x.phase for x in launches}
     assert [x for x in launches if x.lds > x.limit or x.limit > 160 * 1024] == []
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(K=4, Sw=2), dict(p=24, q=1536, L=2),
+                                dict(p=36, q=48, flags=nlpr.STATE_IN)],
+                         ids=["one launch", "two launches", "several items", "resumed"])
+def test_sweeps_need_their_table(run, kw):
+    """The sweep's items are in an order of their own, so its kernels index the table without a
+    look: a launch without one is refused on the host, in every pass, before it is made."""
+    launches, status = run(**kw)
+    grad = kw.get("q", 0) <= 1024 and not kw.get("flags")   # else refused
+    assert set(status.values()) == {nlpr.OK} and ("backward" in status) == grad
+    sweeps = [x for x in launches if "sweep" in x.kernel]
+    assert sweeps and {x.table for x in sweeps} == {"table"}
+    launches, status = run(**kw, more=["no-table"])
+    assert status.pop("create") == nlpr.OK
+    assert set(status.values()) == {nlpr.ERR_HIP}
+    assert not any("sweep" in x.kernel for x in launches)

@@ -625,31 +625,26 @@ int autotune_fft(Plan& P) {
   float* d_real = nullptr;
   float2* d_cplx = nullptr;
   SceneDesc* d_sd = nullptr;
-  int2* d_items = nullptr;
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  const int maxitems = std::max(p, q) * tp;
   int rc = NLPR_OK;
   auto cleanup = [&]() {
     hipFree(d_real);
     hipFree(d_cplx);
     hipFree(d_sd);
-    hipFree(d_items);
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);
   };
   if (hipMalloc(&d_real, 2 * tp * plane * sizeof(float)) != hipSuccess ||
       hipMalloc(&d_cplx, tp * plane * sizeof(float2)) != hipSuccess ||
       hipMalloc(&d_sd, sizeof(SceneDesc)) != hipSuccess ||
-      hipMalloc(&d_items, maxitems * sizeof(int2)) != hipSuccess ||
       hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     cleanup();
     set_error("autotune: allocation failed");
     return NLPR_ERR_HIP;
   }
   hipMemset(d_real, 0, 2 * tp * plane * sizeof(float));
-  std::vector<int2> items(maxitems);
-  for (int i = 0; i < maxitems; ++i) items[i] = make_int2(0, i);
-  hipMemcpy(d_items, items.data(), maxitems * sizeof(int2), hipMemcpyHostToDevice);
+  // no work-item table, as in a solve of one scene: the workgroups run in its order (work_item_xcd)
+  const int2* const items = nullptr;
   SceneDesc h{};
   h.p = p;
   h.q = q;
@@ -693,9 +688,9 @@ int autotune_fft(Plan& P) {
       const int nb = ceil_div(p, lpb) * tp;
       const size_t lds = rows_bytes(q, lpb);
       const float ms = time_it([&]() {
-        hipLaunchKernelGGL(fft_rows_fwd, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items, (int)B_C,
+        hipLaunchKernelGGL(fft_rows_fwd, dim3(nb), dim3(bs), lds, nullptr, d_sd, items, (int)B_C,
                            (int)B_F);
-        hipLaunchKernelGGL(fft_rows_inv<false>, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items, (int)B_F,
+        hipLaunchKernelGGL(fft_rows_inv<false>, dim3(nb), dim3(bs), lds, nullptr, d_sd, items, (int)B_F,
                            (int)B_Z, -1);
       });
       if (hipGetLastError() != hipSuccess) { rc = NLPR_ERR_HIP; break; }
@@ -715,7 +710,7 @@ int autotune_fft(Plan& P) {
       const int nb = ceil_div(q, cb) * tp;
       const size_t lds = cols_bytes(p, cb, dfu);
       const float ms = time_it([&]() {
-        hipLaunchKernelGGL(fft_cols_solve, dim3(nb), dim3(bs), lds, nullptr, d_sd, d_items,
+        hipLaunchKernelGGL(fft_cols_solve, dim3(nb), dim3(bs), lds, nullptr, d_sd, items,
                            (int)B_F);
       });
       if (hipGetLastError() != hipSuccess) { rc = NLPR_ERR_HIP; break; }

@@ -70,3 +70,14 @@ def test_sweeps_need_their_table(run, kw):
     assert status.pop("create") == nlpr.OK
     assert set(status.values()) == {nlpr.ERR_HIP}
     assert not any("sweep" in x.kernel for x in launches)
+
+
+@pytest.mark.parametrize("kw", [dict(p=96, q=64, L=31), dict(p=48, q=48, d=4, flags=nlpr.FUSED_S)],
+                         ids=["plain", "fused-S"])
+def test_tuner_times_the_order_that_the_solve_runs(run, kw):
+    """The passes of the X-update run without a table in a solve of one scene, in the order that
+    keeps neighbouring work items on one XCD; their shapes are tuned in the same order."""
+    launches, _ = run(**kw)
+    tables = {p: {x.table for x in launches if x.phase == p and "fft_" in x.kernel}
+              for p in ("create", "solve")}
+    assert tables == {"create": {"null"}, "solve": {"null"}}

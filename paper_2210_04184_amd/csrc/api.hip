@@ -143,10 +143,10 @@ bool separable_factors(const float* b, int r, std::vector<float>& uv) {
   return true;
 }
 
-// Validate, upload the blur taps and R, precompute the tables, tune the FFT shapes and lay
-// out the scene's part of the workspace.
+// Validate, upload the blur taps and R, precompute the tables, choose the FFT shapes (timed for a
+// scene alone, by rule for one of several) and lay out the scene's part of the workspace.
 int scene_create(const nlpr_params& prm, const float* blur_host, const float* R_host,
-                 const float* E_host, Plan** out) {
+                 const float* E_host, bool alone, Plan** out) {
   *out = nullptr;
   int rc = validate(prm);
   if (rc) return rc;
@@ -252,7 +252,9 @@ int scene_create(const nlpr_params& prm, const float* blur_host, const float* R_
     return cleanup(NLPR_ERR_HIP);
   }
   if ((rc = launch_precompute(*P))) return cleanup(rc);
-  if ((rc = fft_prepare(*P)) || (rc = autotune_fft(*P))) return cleanup(rc);
+  if ((rc = fft_prepare(*P))) return cleanup(rc);
+  if (!alone) batch_fft_shape(*P);
+  else if ((rc = autotune_fft(*P))) return cleanup(rc);
   // workspace layout
   size_t off = 0;
   auto take = [&](int slot, size_t bytes) {
@@ -528,8 +530,6 @@ int batch_build(Batch& B) {
         (rc = sweep_bwd_prepare(P.prm.K)))
       return rc;
   }
-  if (n > 1)
-    for (Plan* P : B.scenes) batch_fft_shape(*P);
   if ((rc = simple(KD_ROWS, rows_blocks, rows_lds, rows_block))) return rc;
   if ((rc = simple(KD_COLS, cols_blocks, cols_lds, cols_block))) return rc;
   // the sweep: one launch per (patch radius, tile size)
@@ -1195,7 +1195,7 @@ int batch_create(Batch& B, int n, const nlpr_params* params, const float* const*
   B.use_graph = (bf & NLPR_GRAPH) != 0;
   for (int i = 0; i < n; ++i) {
     Plan* P = nullptr;
-    int rc = scene_create(params[i], blur[i], R[i], E ? E[i] : nullptr, &P);
+    int rc = scene_create(params[i], blur[i], R[i], E ? E[i] : nullptr, n == 1, &P);
     if (rc) {
       batch_release(B);
       return rc;

@@ -9,10 +9,12 @@
 // The 2-D transform runs as three passes over a complex [pairs][p][q] buffer:
 //   rows_fwd   : pack two bands, forward DFT along every row
 //   cols_solve : forward DFT along columns, multiply by 1/(den p q), inverse DFT along
-//                columns (the column data stays in LDS between the two transforms)
+//                columns (between the two transforms the points stay in registers at powers of
+//                2, in LDS else)
 //   rows_inv   : inverse DFT along rows, unpack the two bands
-// Every pass runs over a batch of scenes (see nlpr_internal.h); lines per block and columns
-// per block are picked per image size by timing candidates when a plan is created.
+// Every pass runs over a batch of scenes (see nlpr_internal.h).  Lines per block and columns per
+// block are picked per image size: for a scene alone by timing candidates when its plan is
+// created, for the scenes of a batch by rule (batch_fft_shape).
 // Each 1-D transform is a Stockham autosort FFT (mixed radix 2/3/4/8): every stage reads R
 // values strided by n/R, twiddles them, does an R-point DFT and writes them to their
 // natural-order position, so no bit reversal is needed.  The first stage reads global memory

@@ -445,6 +445,6 @@ int fft_block(int tpl);             // workgroup size of a line FFT with tpl thr
 int fft_prepare(const Plan& P);     // kernel attributes of the X-update; before its launches
 int autotune_fft(Plan& P);          // picks P.fft by timing candidates (cached per (p, q, d if fused))
 FftShape default_fft_shape(int p, int q, int d_fused);
-void batch_fft_shape(Plan& P);      // P.fft of a scene of a batch
+void batch_fft_shape(Plan& P);      // P.fft of a scene of a batch of several
 
 }  // namespace nlpr

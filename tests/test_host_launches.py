@@ -81,3 +81,11 @@ def test_tuner_times_the_order_that_the_solve_runs(run, kw):
     tables = {p: {x.table for x in launches if x.phase == p and "fft_" in x.kernel}
               for p in ("create", "solve")}
     assert tables == {"create": {"null"}, "solve": {"null"}}
+
+
+@pytest.mark.parametrize("flags", [0, nlpr.FUSED_S], ids=["plain", "fused-S"])
+def test_a_batch_is_made_without_timing_shapes_it_does_not_use(run, flags):
+    """Scenes of a batch take the shapes of a rule: making one launches no pass of the X-update."""
+    launches, status = run(n=3, p=48, q=36, d=4, flags=flags)
+    assert set(status.values()) == {nlpr.OK}
+    assert {x.phase for x in launches if "fft_" in x.kernel} == {"solve"}

@@ -46,9 +46,18 @@ __global__ void twiddle_kernel(float2* twp, int p, float2* twq, int q) {
 // Bound by the FP64 sines: a workgroup takes FREQ frequencies and spreads the terms of each
 // over 256 / FREQ threads, which leave them in LDS; one thread per frequency adds them up in
 // term order.  With one thread per frequency 128 x 128 had one wave per CU, and two 64-bit
-// remainders per term: 47.7 us, now 14.4; 96 x 96 31.8 and 9.3; 1024 x 1024 438 and 437.  FREQ = 64 where
-// the frequencies alone fill the GPU: the adding is done by a whole wave (1024 x 1024 with 16:
-// 392 us).
+// remainders per term.  FREQ = 16 spreads the terms of few frequencies over more threads; with 64
+// the adding is done by a whole wave.  Launch times in us on an MI355X, one thread per frequency /
+// FREQ = 16 / 64, for a 7 x 7 blur with a 3 x 3 window (53 terms) and a 17 x 17 blur with a
+// 7 x 7 window (313 terms):
+//    64 x 64       28 /   6 /   9      151 /   22 /   40
+//   128 x 128      31 /  10 /   9      164 /   35 /   41
+//   192 x 192      41 /  18 /  17      221 /   67 /   79
+//   256 x 256      42 /  28 /  21      224 /  110 /  104
+//   512 x 512      70 /  99 /  69      387 /  403 /  365
+//   1024 x 1024   243 / 376 / 259     1332 / 1493 / 1353
+// so 64 from 2^16 frequencies on.  (With a 3 x 3 blur and window, 13 terms, 256 x 256 takes 13, 13
+// and 8 us and 1024 x 1024 63, 160 and 75.)
 template <int FREQ>
 __global__ void __launch_bounds__(256)
 den_kernel(float* invden, int p, int q, const float* blur, int r, const int2* taus, int npairs,
@@ -843,9 +852,10 @@ int launch_precompute(Plan& P) {
   hipLaunchKernelGGL(twiddle_kernel, dim3(ceil_div(std::max(p, q), 256), 2), dim3(256), 0, nullptr,
                      P.d_tw_p, p, P.d_tw_q, q);
   NLPR_LAUNCH_CHECK("twiddle_kernel");
-  const bool many = (size_t)p * q >= (size_t)1 << 17;
+  const bool many = (size_t)p * q >= (size_t)1 << 16;
   hipLaunchKernelGGL(many ? den_kernel<64> : den_kernel<16>, dim3(ceil_div(q, many ? 64 : 16), p),
-                     dim3(256), 0, nullptr, P.d_invden, p, q, P.d_blur, P.prm.blur_radius, P.d_taus, P.npairs, P.npatch);
+                     dim3(256), 0, nullptr, P.d_invden, p, q, P.d_blur, P.prm.blur_radius, P.d_taus,
+                     P.npairs, P.npatch);
   NLPR_LAUNCH_CHECK("den_kernel");
   if (P.d_E) {
     hipLaunchKernelGGL(subspace_kernel, dim3(1), dim3(256), 0, nullptr, P.d_E, P.d_R, P.prm.L, P.Lx,

@@ -89,3 +89,13 @@ def test_a_batch_is_made_without_timing_shapes_it_does_not_use(run, flags):
     launches, status = run(n=3, p=48, q=36, d=4, flags=flags)
     assert set(status.values()) == {nlpr.OK}
     assert {x.phase for x in launches if "fft_" in x.kernel} == {"solve"}
+
+
+@pytest.mark.parametrize("p,q,freq", [(8, 12, 16), (192, 324, 16), (256, 256, 64), (243, 324, 64),
+                                      (1024, 96, 64)])
+def test_denominator_variant(run, p, q, freq):
+    """Frequencies per workgroup on both sides of the line, and workgroups for all of them."""
+    launches, _ = run(p=p, q=q, d=1, iters=0)
+    (den,) = [x for x in launches if "den_kernel" in x.kernel]
+    assert f"den_kernelILi{freq}E" in den.kernel
+    assert (den.grid - 1) * freq < q <= den.grid * freq and den.block == 256

@@ -381,7 +381,6 @@ void batch_release(Batch& B) {
 // 256 x 256 x 31, 32 -> 20 us at 1024 x 1024 x 4.  (The blur's reads at 256 x 256 x 31 were
 // 3.05 times its input with the bands spread over the XCDs, 1.06 times like this.)
 void xcd_append(std::vector<int2>& out, const std::vector<int2>& items) {
-  constexpr int kXcds = 8;
   const int n = (int)items.size(), o = (int)out.size();
   int next[kXcds], sum = 0;
   for (int x = 0; x < kXcds; ++x) {       // XCD x: the positions b in [o, o + n), b % 8 == x
@@ -394,7 +393,6 @@ void xcd_append(std::vector<int2>& out, const std::vector<int2>& items) {
 // The sweep's items y = (tile * split + part) * L + band in that order; within an XCD's range
 // the bands are fastest, so that workgroups resident together share the tile's thresholds.
 std::vector<int2> sweep_items(const Plan& P, int scene, int offset) {
-  constexpr int kXcds = 8;
   const int parts = P.sweep.ntiles * P.sweep.split, n = parts * P.Lx;
   std::vector<int2> items;
   items.reserve(n);

@@ -99,6 +99,7 @@ struct SceneDesc {
   void* buf[B_COUNT];
 };
 
+constexpr int kXcds = 8;             // workgroup b of a launch runs on XCD b % kXcds
 constexpr int kSweepThreads = 256;   // workgroup size of the sweep
 // Batches of at least this many pixel-bands (summed over scenes) run the P-side of each
 // iteration on a second stream, concurrently with the sweep.  Below it the two cross-stream

@@ -99,3 +99,14 @@ def test_denominator_variant(run, p, q, freq):
     (den,) = [x for x in launches if "den_kernel" in x.kernel]
     assert f"den_kernelILi{freq}E" in den.kernel
     assert (den.grid - 1) * freq < q <= den.grid * freq and den.block == 256
+
+
+@pytest.mark.parametrize("p,q,parts", [(8, 8, 4), (18, 108, 4), (48, 64, 4), (96, 96, 4),
+                                       (324, 384, 4), (384, 384, 1)])
+def test_p_update_covers_its_items_by_xcd(run, p, q, parts):
+    """With several workgroups per work item of 256 pixels, workgroup b takes part b / 8 of one of
+    eight items, on the XCD (b % 8) of the item's index: whole groups of eight are launched."""
+    items = -(-p * q // 256)
+    launches, _ = run(p=p, q=q, d=1, iters=2, flags=nlpr.TIMING)
+    grids = {x.grid for x in launches if "pupdate_kernel" in x.kernel}
+    assert grids == {items if parts == 1 else -(-items // 8) * 8 * parts}

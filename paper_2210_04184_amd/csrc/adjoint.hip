@@ -900,7 +900,7 @@ template <int K>
 int launch_sbwd(const Batch& B, const Group& g, size_t lds, int cb, const uint8_t* codes, int sb,
                 int xr, int halo, int mup, const uint8_t* pcodes, int cbp, const PbSlots* pb,
                 hipStream_t s) {
-  return g.policy == kSweepCached
+  return g.grad_policy == kSweepCached
              ? launch_sbwd_policy<K, true>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s)
              : launch_sbwd_policy<K, false>(B, g, lds, cb, codes, sb, xr, halo, mup, pcodes, cbp, pb, s);
 }

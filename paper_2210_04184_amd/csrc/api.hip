@@ -530,6 +530,13 @@ int batch_build(Batch& B) {
   }
   if ((rc = simple(KD_ROWS, rows_blocks, rows_lds, rows_block))) return rc;
   if ((rc = simple(KD_COLS, cols_blocks, cols_lds, cols_block))) return rc;
+  size_t pbands = 0, all = 0;              // pixel-bands and bytes of dual state of the batch
+  bool reg = false;
+  for (const Plan* P : B.scenes) {
+    pbands += (size_t)P->prm.p * P->prm.q * P->Lx;
+    all += P->sz[B_SIGMA] + P->sz[B_SCODE];
+    reg = reg || P->npairs > 0;
+  }
   // the sweep: one launch per (patch radius, tile size)
   for (int K = 0; K <= kMaxK; ++K)
     for (int items = 1; items <= 4; items *= 2) {
@@ -546,7 +553,10 @@ int batch_build(Batch& B) {
       }
       if (it.empty()) continue;
       if ((rc = add_group(B, KD_SWEEP, it, kSweepThreads, l, K, items))) return rc;
-      B.groups[KD_SWEEP].back().policy = sweep_policy(state, planes);
+      Group& g = B.groups[KD_SWEEP].back();
+      g.policy = sweep_policy(state, planes, all, pbands);
+      // (a reverse pass goes through its checkpoints, which no L2 holds)
+      g.grad_policy = sweep_policy(state, planes, state, SIZE_MAX);
       if ((rc = sweep_prepare(K, items))) return rc;
     }
   // work-item tables, descriptors, the finite check's flag and the open-item counters: one
@@ -573,12 +583,6 @@ int batch_build(Batch& B) {
   if (n > 1) NLPR_HIP_TRY(hipHostMalloc(&B.h_desc, n * sizeof(SceneDesc)));
   NLPR_HIP_TRY(hipEventCreateWithFlags(&B.upload_ev, hipEventDisableTiming));
   NLPR_HIP_TRY(hipEventCreateWithFlags(&B.done_ev, hipEventDisableTiming));
-  size_t pbands = 0;
-  bool reg = false;
-  for (const Plan* P : B.scenes) {
-    pbands += (size_t)P->prm.p * P->prm.q * P->Lx;
-    reg = reg || P->npairs > 0;
-  }
   const Plan& P0 = *B.scenes[0];
   const bool one = sweep_pu(B) && !P0.d_E && (size_t)P0.prm.p * P0.prm.q < kForkPixels;
   if (reg && !B.timing && pbands >= kForkPixelBands && !one) {

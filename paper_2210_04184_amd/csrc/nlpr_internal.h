@@ -179,6 +179,7 @@ struct Group {
   size_t lds = 0;
   int key0 = 0, key1 = 0;   // sweep: K, items per thread
   int policy = 0;           // sweep: cache policy of the dual state
+  int grad_policy = 0;      // the same in reverse mode: branch-recording sweep and its adjoint
 };
 
 enum Kind { KD_WEIGHTS = 0, KD_PLANE, KD_CONV, KD_PIXEL, KD_SWEEP, KD_ROWS, KD_COLS,
@@ -439,7 +440,7 @@ int sweep_prepare(int K, int items);   // kernel attributes; before launches or 
 
 // ---- shapes and tuning
 SweepShape choose_sweep_shape(int p, int q, int K, int halo);
-int sweep_policy(size_t state, int planes);
+int sweep_policy(size_t state, int planes, size_t all, size_t pbands);
 int choose_pair_split(int blocks, int npairs);   // SweepShape.split for `blocks` (tile, band) pairs
 size_t sweep_sigma_bytes(const SweepShape& sh, int q, int L, int npairs, int npatch);
 int fft_block(int tpl);             // workgroup size of a line FFT with tpl threads per line

@@ -686,7 +686,8 @@ int set_lds_limit_items(int items) {
   }
 }
 
-// g.key1 = tile items, g.policy = the cache policy of single-item tiles
+// g.key1 = tile items; the cache policy of single-item tiles
+inline int policy_of(const Group& g, const uint8_t* codes) { return codes ? g.grad_policy : g.policy; }
 template <int K, bool FIRST, int POLICY>
 int launch_single(const Batch& B, const Group& g, int x, int mu, int sig, int creg, int halo,
                   uint8_t* codes, unsigned long long* count, hipStream_t s) {
@@ -705,7 +706,7 @@ int launch_items(const Batch& B, const Group& g, int x, int mu, int sig, int cre
   }
   switch (g.key1) {
     case 1:
-      switch (g.policy) {
+      switch (policy_of(g, codes)) {
         case kSweepCached:
           return launch_single<K, FIRST, kSweepCached>(B, g, x, mu, sig, creg, halo, codes, count, s);
         case kSweepCodesCached:
@@ -734,7 +735,7 @@ int launch_kpu(const Batch& B, const Group& g, const Group& gp, const PuSlots& s
 template <int K>
 int launch_pu_k(const Batch& B, const Group& g, const Group& gp, const PuSlots& sl, int x, int mu,
                 int sig, int creg, int halo, uint8_t* codes, hipStream_t s) {
-  switch (g.policy) {
+  switch (policy_of(g, codes)) {
     case kSweepCached:
       return codes ? launch_kpu<K, true, kSweepCached>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s)
                    : launch_kpu<K, false, kSweepCached>(B, g, gp, sl, x, mu, sig, creg, halo, codes, s);
@@ -795,22 +796,33 @@ int choose_pair_split(int blocks, int npairs) {
   return std::min(npairs, (kCus + blocks - 1) / blocks);
 }
 
-// Cache policy of a sweep launch over `state` bytes of dual state (capacity, all scenes) with
-// `planes` planes per band.  The lines lie where they are measured; sweep per launch, MI355X:
-// - up to 384 MB, of which a launch touches about half, the state stays in the 256 MB
-//   Infinity Cache from one sweep to the next when it is not streamed: 256 x 256 x 31 3x3/3x3
-//   (312 MB) 65 us streamed, 54 us cached; 192 x 256 x 31 (233 MB) 51 and 40 us; but
-//   256 x 256 x 46 (461 MB) 3.74 and 3.79 ms per 20-iteration solve, and 1024 x 1024 x 4 with a
-//   5x5 window (1.9 GB) 597 and 727 us.
-// - above that the values are streamed.  The code bytes (1/17 of the state, read and written
+// Cache policy of a sweep launch over `state` bytes of dual state (capacity) with `planes` planes
+// per band, in a batch with `all` bytes of state and `pbands` pixel-bands.  The lines lie where they
+// are measured, on an MI355X:
+// - up to 384 MB, of which an iteration touches about half, the state stays in the 256 MB
+//   Infinity Cache from one sweep to the next when it is not streamed; sweep per launch:
+//   256 x 256 x 31 3x3/3x3 (312 MB) 65 us streamed, 54 us cached; 192 x 256 x 31 (233 MB) 51 and
+//   40 us; but 256 x 256 x 46 (461 MB) 3.74 and 3.79 ms per 20-iteration solve, and
+//   1024 x 1024 x 4 with a 5x5 window (1.9 GB) 597 and 727 us.  The launches of a batch share that
+//   cache: 24 scenes with 3x3 and 5x5 patches, 294 and 310 MB in two launches, 2.27 ms per solve
+//   streamed, 2.77 cached.
+// - below 2^19 pixel-bands the ten planes that the other stages pass on stay in the 32 MB of L2,
+//   from which a cached state, read or written, pushes them.  Solves of 10 iterations there, streamed
+//   and cached, in us: 64 x 64 x 8 5x5/7x7 (80 MB) 496 and 563, 128 x 128 x 31 3x3/3x3 (74 MB) 500
+//   and 534, 96 x 96 x 8 9x9/3x3 (97 MB) 621 and 702; from about 192 MB of state on cached is the
+//   better as often as not: 192 x 192 x 8 5x5/5x5 (359 MB) 1282 and 1229, 16 x 512 x 6 7x7/7x7
+//   (234 MB) 1110 and 937, 64 x 64 x 8 9x9/7x7 (258 MB) 970 and 1001.  Above 2^19:
+//   256 x 256 x 16 3x3/3x3 (153 MB) 734 and 713, 512 x 512 x 3 3x3/3x3 (115 MB) 818 and 789.
+// - otherwise the values are streamed.  The code bytes (1/17 of the state, read and written
 //   64 bytes per wave) gain from the caches, which also join stores that are not whole 64-byte
 //   blocks: 108 x 144 x 31 5x5/5x5 151 us streamed, 139 us cached; 512 x 512 x 16 5x5/11x11
 //   2.91 and 2.83 ms.  But they push the dense planes out of the caches, which counts where the
 //   sweep does not carry the iteration: 256 x 256 x 124 3x3/3x3 (1.2 GB) 9.1 ms per solve
 //   streamed, 9.5 ms cached.  So the codes are streamed for more than 1 GB of state in planes
 //   so few (under 200) that the other stages matter.
-int sweep_policy(size_t state, int planes) {
-  if (state <= (size_t)384 << 20) return kSweepCached;
+int sweep_policy(size_t state, int planes, size_t all, size_t pbands) {
+  const bool l2 = pbands < (size_t)1 << 19;
+  if (all <= (size_t)384 << 20 && (!l2 || all >= (size_t)192 << 20)) return kSweepCached;
   if (state <= (size_t)1 << 30 || planes >= 200) return kSweepCodesCached;
   return kSweepStream;
 }

@@ -110,3 +110,30 @@ def test_p_update_covers_its_items_by_xcd(run, p, q, parts):
     launches, _ = run(p=p, q=q, d=1, iters=2, flags=nlpr.TIMING)
     grids = {x.grid for x in launches if "pupdate_kernel" in x.kernel}
     assert grids == {items if parts == 1 else -(-items // 8) * 8 * parts}
+
+
+def _policies(launches, phase):
+    """Cache policies (last template argument) of the sweeps of a phase."""
+    return {int(x.kernel.split("ELi")[-1].split("E")[0]) for x in launches
+            if x.phase == phase and ("12sweep_kernel" in x.kernel or "sweep_pu_kernel" in x.kernel)}
+
+
+@pytest.mark.parametrize("kw,solve,forward",
+                         [(dict(p=64, q=64, L=8, K=2, Sw=3), 1, 0),           # 80 MB of state
+                          (dict(p=128, q=128, L=31, K=1, Sw=1), 1, 0),        # 2^19 - 16384 pixel-bands
+                          (dict(p=128, q=128, L=32, K=1, Sw=1), 0, 0),        # 2^19
+                          (dict(p=96, q=96, L=8, K=2, Sw=3), 1, 0),           # 179 MB
+                          (dict(p=192, q=192, L=8, K=2, Sw=2), 0, 0),         # 358 MB, below 2^19
+                          (dict(p=64, q=64, L=8, K=3, Sw=5), 1, 1),           # 390 MB
+                          (dict(p=256, q=256, L=37, K=1, Sw=1), 0, 0),        # 354 MB, above 2^19
+                          (dict(p=256, q=256, L=124, K=1, Sw=1), 2, 2),       # 1.2 GB in 36 planes
+                          (dict(p=128, q=128, L=32, K=1, Sw=1, n=4), 0, None),
+                          (dict(p=128, q=128, L=32, K=1, Sw=1, n=6), 1, None)],
+                         ids=lambda v: "-".join(map(str, v.values())) if isinstance(v, dict) else str(v))
+def test_cache_policy_of_the_sweep(run, kw, solve, forward):
+    """0: the dual state cached, 1: its values streamed, 2: all streamed, by its bytes, the planes
+    per band and the pixel-bands of the whole batch; reverse mode by the bytes and planes alone."""
+    launches, _ = run(d=1, iters=2, **kw)
+    assert _policies(launches, "solve") == {solve}
+    if forward is not None:
+        assert _policies(launches, "forward") == {forward}

@@ -60,8 +60,6 @@ __device__ __forceinline__ void st_nt(gfloat* p, float4 v) {
   *(gv4f*)p = w;
 #endif
 }
-// class mask: not a number, infinite or zero
-constexpr int kNoSign = 0x267;
 __device__ __forceinline__ float clampf(float v, float m) { return fminf(fmaxf(v, -m), m); }
 
 // ---- sweep kernel begin (the traffic record of the benchmark is keyed to this text)
@@ -483,27 +481,23 @@ sweep_body(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int
           }
           // the code byte, shifted in one bit at a time (alignbit(c, x, 31) = c << 1 | x >> 31):
           // the off flags (sign bits of |V| - mu) of elements 3..0, then the signs of V
-          float off[4];
 #pragma unroll
-          for (int e = 3; e >= 0; --e) {
-            off[e] = fabsf(vv[e]) - mu4[e];
-            code = __builtin_amdgcn_alignbit(code, __float_as_uint(off[e]), 31);
-          }
+          for (int e = 3; e >= 0; --e)
+            code = __builtin_amdgcn_alignbit(code, __float_as_uint(fabsf(vv[e]) - mu4[e]), 31);
 #pragma unroll
           for (int e = 3; e >= 0; --e)
             code = __builtin_amdgcn_alignbit(code, __float_as_uint(vv[e]), 31);
           if (CODES) {
             // the branches from the code byte: on the threshold with the sign clear (1) or set
-            // (2), bits e spread to bits 2e.  That is what the comparisons say where |V| - mu is
-            // neither 0, infinite nor a NaN (a threshold may be one, from a NaN in Y_h); a wave
-            // with any other element takes them from the comparisons
+            // (2), bits e spread to bits 2e.  A wave with a V or a mu that is not a number (mu from
+            // a NaN in Y_h), or with both 0, takes them from the comparisons
             unsigned w = (~code >> 4 & ~code & 15u) | (~code >> 4 & code & 15u) << 16;
             w = (w | w << 2) & 0x00330033u;
             w = (w | w << 1) & 0x00550055u;
             branch = w | w >> 15;
             bool odd = false;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) odd |= __builtin_amdgcn_classf(off[e], kNoSign);
+            for (int e = 0; e < 4; ++e) odd |= !(fabsf(vv[e]) > -mu4[e]);
             if (__builtin_amdgcn_ballot_w64(odd)) {
               branch = 0;
 #pragma unroll

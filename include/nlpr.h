@@ -178,7 +178,8 @@ int nlpr_workspace_size(const nlpr_plan* plan, size_t* bytes);
  *   ws : device workspace of at least nlpr_workspace_size() bytes, 256-byte aligned.  It
  *        holds the ADMM state on return, so a later call with NLPR_STATE_IN continues the
  *        iteration (T1 iterations then T2 resumed iterations give the same Z, bit for bit,
- *        as T1 + T2 iterations at once).
+ *        as T1 + T2 iterations at once).  A resumed solve uses the state it finds as it is,
+ *        Lambda1 on every pixel included.
  * Never allocates device memory.  Asynchronous on `stream` unless NLPR_CHECK_FINITE is set.
  */
 int nlpr_solve(nlpr_plan* plan, const float* Yl, const float* Yh, float* Z, void* ws,
@@ -379,8 +380,9 @@ int nlpr_monitor(const nlpr_plan* plan, double* trace, int32_t cap, int32_t* n);
  *
  * nlpr_grad_sizes: bytes of the checkpoint buffer and of the gradient workspace.  For
  *   t = 1 .. iters-1 the checkpoints hold X^t, B X^t, the Lambda1 and Lambda2 entering
- *   iteration t (B X^t and Lambda1 at the sampled pixels), and which branch of the threshold every dual element of its sweep took
- *   (2 bits each: |V| < mu, V >= mu or V <= -mu; the adjoint needs nothing else of Sigma).
+ *   iteration t (B X^t and Lambda1 at the sampled pixels), and which branch of the threshold
+ *   every dual element of its sweep took (2 bits each: |V| < mu, V >= mu or V <= -mu; the
+ *   adjoint needs nothing else of Sigma).
  *   They take (iters - 1) * (16 + Npairs |P| / 4) * L * p * q bytes, each part rounded up to
  *   a multiple of 256 (at least 256 in all).
  * nlpr_forward: like nlpr_solve (Z equal bit for bit) and also writes the checkpoints to ck

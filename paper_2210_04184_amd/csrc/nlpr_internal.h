@@ -1,10 +1,11 @@
 // Internal declarations of libnlpr: scene plans, the batch every launch runs over, device
 // scene descriptors and kernel launchers.
 //
-// Every kernel runs over a batch of scenes.  Block b of a launch reads its work item
-// items[b] = (scene, local block), takes the scene's sizes, tables and buffers from the
-// device descriptor sd[scene] and does the work of that local block.  A single-scene plan
-// is a batch of one, so one code path serves both.  Kernels reach buffers through slots
+// Every kernel runs over a batch of scenes.  Block b of a launch has a work item (scene, local
+// block), takes the scene's sizes, tables and buffers from the device descriptor sd[scene] and
+// does the work of that local block.  The items of a batch of several scenes are read from a
+// table, items[b]; a single-scene plan is a batch of one, whose items follow from b (work_item),
+// the sweep's and its adjoint's excepted.  Kernels reach buffers through slots
 // (SceneDesc::buf[slot]), so the same kernel serves the solve and the per-stage entry
 // points with different buffers.
 #pragma once
@@ -112,7 +113,10 @@ constexpr size_t kForkPixelBands = (size_t)1 << 22;
 // iteration, second stream and one launch: 512 x 512 x 24 5x5/5x5 1010 and 910 us, 512 x 512 x 31 3x3/3x3
 // 345 and 323, 512 x 512 x 16 5x5/11x11 2705 and 2595, 768 x 768 x 8 5x5/5x5 940 and 908; but
 // 1024 x 1024 x 4 3x3/3x3 291 and 303, 1024 x 1024 x 8 3x3/5x5 833 and 838, and 512 x 512 with a
-// 20-band basis 2491 and 2497 (there the second stream hides the blur too).
+// 20-band basis 2491 and 2497 (there the second stream hides the blur too).  These are wall times
+// without a tracer.  Under a kernel trace the 1024 x 1024 x 4 scene runs in 450 us per iteration
+// with the P-side inside the sweep, so some of the second stream's cost lies outside the kernels; the
+// line holds as long as that does.
 constexpr size_t kForkPixels = (size_t)1 << 20;
 // Cache policies of the sweep's dual state: nothing, the packed values, or all of it bypass
 // the caches (non-temporal).

@@ -598,10 +598,13 @@ sweep_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, i
 // The sweep (the first nsw workgroups) and the P-update (the rest), which read X and write
 // disjoint buffers.  A P-update of its own is bound by latency up to 256 x 256 (13.9 us for 40 MB at
 // 31 bands) and costs a launch; here its workgroups fill the end of the sweep, whose last
-// workgroups leave CUs idle.  It stays within the sweep's registers (K <= 3), so the sweep's
-// occupancy is the same.  Per iteration of a solve: 64 x 64 x 8 (graph) 36.2 -> 32.2 us, 128 x 128 x 31
-// 65 -> 58, 192 x 256 x 31 fused-S 88 -> 80, 256 x 256 x 31 103 -> 96; with the P-update's
-// workgroups first, 88 -> 90 and 103 -> 102.
+// workgroups leave CUs idle.  At K = 1, 2 and 3 it stays within the sweep's registers, so the sweep's
+// occupancy is the same; at K = 0 it takes 97 where the sweep alone takes 94, four waves per SIMD
+// instead of five, and is still the faster.  Per iteration of a solve, two launches and one:
+// 64 x 64 x 8 (graph) 36.2 and 32.2 us, 128 x 128 x 31 65 and 58, 192 x 256 x 31 fused-S 88 and 80,
+// 256 x 256 x 31 103 and 96; with K = 0, 3x3 window, 128 x 128 x 31 50 and 43, 256 x 256 x 31 85 and
+// 81; with K = 3 105 and 96, 249 and 238.  With the P-update's workgroups first, 88 -> 90 and
+// 103 -> 102.
 template <int K, bool CODES, int POLICY>
 __global__ void __launch_bounds__(256)
 sweep_pu_kernel(const SceneDesc* __restrict__ sd, const int2* __restrict__ items, int x_s,
